@@ -411,8 +411,8 @@ int lesasm_mlp_loss_grad(lesasm_mlp *mlp, const float *d_x, const float *d_t, in
 /* lesasm_mlp_loss_grad without any device allocation, for callers that
  * cannot allocate (code under HIP graph capture, serving loops, harnesses
  * that forbid hipMalloc).  Same arguments, kernels and results (bit for bit)
- * as lesasm_mlp_loss_grad, but the work arrays sit in a static device area of
- * 8192 samples (8.6 MB, held by each device the library runs on until the
+ * as lesasm_mlp_loss_grad, but the work array sits in a static device area for
+ * 8192 samples (2.7 MB, held by each device the library runs on until the
  * process ends): n > 8192 gives LESASM_E_INVALID_ARG and nothing runs.  The
  * area's address is looked up on the first call on each device.  Every call
  * on one device shares that area: calls that overlap on one device (two
