@@ -79,6 +79,7 @@ struct Category {
     uint16_t *d_lf = nullptr;      // [nnode][n] chunk-local field index (aliases d_lg without a field map)
     int32_t *d_fslot = nullptr;    // per d_fnodes entry: staging slot of a shared node, -1 if owned
     int lds_doubles = 0;           // largest LDS footprint of a chunk, in doubles
+    int project_doubles = 0;       // the same for the divergence and gradient kernels
     int chunk_elems = 0;           // chunk length used for this category
     std::vector<int32_t> h_cg, h_cf;  // host copies of the internal connectivity (slot-major)
     std::vector<int32_t> h_fnodes;    // host copy of d_fnodes
@@ -120,6 +121,7 @@ int mesh_order_end(lesasm_mesh *m, hipStream_t s, bool capturing);
 int grid_for(size_t n, int block);
 int assemble_into(lesasm_mesh *m, const double *u, const double *p, double nu, double dt, double *rhs, hipStream_t s,
                   bool increment);
+bool mesh_is_chunked(const lesasm_mesh *m);  // one of the chunked scatters
 int launch_wall(lesasm_mesh *m, const double *u, double nu, double *rhs, hipStream_t s);
 
 // Arguments of one assembly launch over a contiguous element range of a category.

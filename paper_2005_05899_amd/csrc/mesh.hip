@@ -293,7 +293,7 @@ static int build_chunks(lesasm_mesh *m, int k) {
     c.d_lf = nullptr;
     dfree(m, c.d_lg);
     c.n_chunks = 0;
-    c.lds_doubles = 0;
+    c.lds_doubles = c.project_doubles = 0;
     if (c.n == 0) return LESASM_OK;
     const bool periodic = !c.h_cf.empty();
     const std::vector<int32_t> &cg = c.h_cg, &cf = periodic ? c.h_cf : c.h_cg;
@@ -347,6 +347,7 @@ static int build_chunks(lesasm_mesh *m, int k) {
             fslot[f] = -1;
         }
         c.lds_doubles = std::max(c.lds_doubles, (int)(3 * gl.size() + 7 * fl.size()));
+        c.project_doubles = std::max(c.project_doubles, (int)(3 * gl.size() + 4 * fl.size()));
         // chunk node lists are indexed with int32 offsets on the GPU
         if (gnodes.size() >= (size_t)INT32_MAX || fnodes.size() >= (size_t)INT32_MAX)
             return fail(LESASM_E_UNSUPPORTED, "mesh_create: chunk node lists of one element type exceed 2^31 entries");

@@ -166,6 +166,12 @@ template <> struct Modal<LESASM_HEX08> {
         F[6] += z * t[1] + y * t[2];
         F[7] += yz * t[0] + xz * t[1] + xy * t[2];
     }
+    // F_m += phi_m f
+    __host__ __device__ static void test_value(double *F, const double *q, double f) {
+        F[0] += f;
+#pragma unroll
+        for (int m = 1; m < 8; ++m) F[m] += q[m - 1] * f;
+    }
     // R_a = sum_m s^m_a F_m (scale and sign are in the weights)
     template <typename R> __host__ __device__ static void to_nodal(const R (&F)[8], R (&r)[8]) {
         // inverse tensor transform: r[t] = sum over monomials of signs
@@ -239,6 +245,12 @@ template <> struct Modal<LESASM_PEN06> {
         F[4] += z * t[0] + r * t[2];
         F[5] += z * t[1] + s * t[2];
     }
+    // F_m += phi_m f
+    __host__ __device__ static void test_value(double *F, const double *q, double f) {
+        F[0] += f;
+#pragma unroll
+        for (int m = 1; m < 6; ++m) F[m] += q[m - 1] * f;
+    }
     // R_(i,l) = sum_m 2 B[(i,l)][m] F_m (the 1/2 and the sign are in the weights)
     template <typename R> __host__ __device__ static void to_nodal(const R (&F)[6], R (&r)[6]) {
         const R a = F[0] - F[1] - F[2], b = F[3] - F[4] - F[5];
@@ -284,6 +296,12 @@ template <> struct Modal<LESASM_PYR05> {
         F[2] += t[1];
         F[3] += t[2];
         F[4] += (R)q[5] * t[0] + (R)q[4] * t[1] + (R)q[6] * t[2];
+    }
+    // F_m += phi_m f
+    __host__ __device__ static void test_value(double *F, const double *q, double f) {
+        F[0] += f;
+#pragma unroll
+        for (int m = 1; m < 5; ++m) F[m] += q[m - 1] * f;
     }
     template <typename R> __host__ __device__ static void to_nodal(const R (&F)[5], R (&r)[5]) {
         const R b = F[0] - F[3];

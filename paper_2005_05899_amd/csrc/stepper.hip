@@ -145,6 +145,196 @@ __global__ __launch_bounds__(256) void k_gradient(CatView c, const double *__res
         for (int i = 0; i < 3; ++i) unsafeAtomicAdd(out + 3 * (size_t)fid[a] + i, m[a][i]);
 }
 
+// ---- the same operators on chunked meshes ---------------------------------------
+//
+// The kernels above add every element's nodes with device atomics (28 G/s:
+// 1.2 ms for the gradient of a 2.0 M-element box, whose bytes take 0.02 ms).
+// Meshes with chunks use these instead: one launch over the chunks of all four
+// types, a chunk's nodes staged in LDS and its contributions summed there
+// (LDS atomics), nodes owned by the chunk stored and only shared ones added
+// with device atomics into the zeroed output.  They keep nothing between the
+// calls (in particular not the mesh's staging rows), so calls on several
+// streams stay independent.  With adj = det J^-1 the quadrature sums
+//   (D u)_a = sum_g w N_a tr(Gx adj),   (G p)_a = sum_g w N_a px adj
+// need no division; nodes enter (relative to the element's node 0, as above)
+// and leave through the modal coefficients.
+// 2.0 M hybrid box: gradient 87 us against 1200 (four kernels), divergence 66
+// against 307.  One thread per output entry in the write-back, not per node, so
+// that a wavefront's atomics fill cache lines: gradient 87 against 139 us.
+template <int T, bool GRAD, class XA, class VA>
+__device__ __forceinline__ void element_project(XA xa, VA va, double (&r)[GRAD ? 3 : 1][Ref<T>::nn]) {
+    constexpr int nn = Ref<T>::nn, NI = GRAD ? 1 : 3, NO = GRAD ? 3 : 1;
+    auto adjugate = [](const double (&J)[3][3], double (&adj)[3][3]) {
+        adj[0][0] = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+        adj[0][1] = J[0][2] * J[2][1] - J[0][1] * J[2][2];
+        adj[0][2] = J[0][1] * J[1][2] - J[0][2] * J[1][1];
+        adj[1][0] = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+        adj[1][1] = J[0][0] * J[2][2] - J[0][2] * J[2][0];
+        adj[1][2] = J[0][2] * J[1][0] - J[0][0] * J[1][2];
+        adj[2][0] = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+        adj[2][1] = J[0][1] * J[2][0] - J[0][0] * J[2][1];
+        adj[2][2] = J[0][0] * J[1][1] - J[0][1] * J[1][0];
+    };
+    // weight times the operator's value at a point, from the reference gradients of the input
+    auto point = [](const double (&g)[NI][3], const double (&adj)[3][3], double w, double (&f)[NO]) {
+        if constexpr (GRAD) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) f[i] = w * (g[0][0] * adj[0][i] + g[0][1] * adj[1][i] + g[0][2] * adj[2][i]);
+        } else {
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) s += g[i][j] * adj[j][i];
+            f[0] = w * s;
+        }
+    };
+    if constexpr (T == LESASM_TET04) {  // constant gradients: sum_g w_g N_a(g) = 1/24
+        double J[3][3], g[NI][3], adj[3][3], f[NO];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) J[i][k] = xa(k + 1, i) - xa(0, i);
+#pragma unroll
+            for (int i = 0; i < NI; ++i) g[i][k] = va(k + 1, i) - va(0, i);
+        }
+        adjugate(J, adj);
+        point(g, adj, 1.0 / 24.0, f);
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) r[o][a] = f[o];
+    } else {
+        using M = Modal<T>;
+        constexpr int nm = M::nm;
+        double X[3][nm], C[NI][nm], F[NO][nm], v[nn];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+#pragma unroll
+            for (int a = 0; a < nn; ++a) v[a] = xa(a, i) - xa(0, i);
+            M::to_modal(v, X[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+#pragma unroll
+            for (int a = 0; a < nn; ++a) v[a] = va(a, i) - va(0, i);
+            M::to_modal(v, C[i]);
+        }
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+#pragma unroll
+            for (int m = 0; m < nm; ++m) F[o][m] = 0.0;
+        const auto &pt = M::pts();
+#pragma unroll 1
+        for (int gp = 0; gp < M::ng; ++gp) {
+            const double *q = pt.q[gp];
+            double J[3][3], g[NI][3], adj[3][3], f[NO];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) M::grad(X[i], q, J[i]);
+#pragma unroll
+            for (int i = 0; i < NI; ++i) M::grad(C[i], q, g[i]);
+            adjugate(J, adj);
+            point(g, adj, -pt.w[gp], f);  // (the weights carry the residual's sign)
+#pragma unroll
+            for (int o = 0; o < NO; ++o) M::test_value(F[o], q, f[o]);
+        }
+#pragma unroll
+        for (int o = 0; o < NO; ++o) M::to_nodal(F[o], r[o]);
+    }
+}
+
+struct ProjectView {
+    ChunkView v[kNumCat];      // in launch order
+    int first[kNumCat + 1];    // workgroups [first[k], first[k + 1]) take the chunks of v[k]
+};
+
+template <int T, bool GRAD, bool PERIODIC>
+__device__ __forceinline__ void project_chunk(const ChunkView &c, int j, double *lds, const double *__restrict__ xyz,
+                                              const double *__restrict__ in, double *__restrict__ out) {
+    constexpr int nn = Ref<T>::nn, NI = GRAD ? 1 : 3, NO = GRAD ? 3 : 1;
+    const int e0 = c.eoff[j], e1 = c.eoff[j + 1];
+    const int g0 = c.goff[j], ng = c.goff[j + 1] - g0;
+    const int f0 = PERIODIC ? c.foff[j] : g0;
+    const int nf = PERIODIC ? c.foff[j + 1] - f0 : ng;
+    double *sx = lds, *sv = sx + 3 * ng, *sacc = sv + NI * nf;
+    for (int k = threadIdx.x; k < ng; k += blockDim.x) {
+        const size_t g = (size_t)c.gnodes[g0 + k];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) sx[3 * k + i] = xyz[3 * g + i];
+    }
+    for (int k = threadIdx.x; k < nf; k += blockDim.x) {
+        const size_t f = (size_t)((uint32_t)c.fnodes[f0 + k] & ~kOwnedBit);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) sv[NI * k + i] = in[NI * f + i];
+#pragma unroll
+        for (int o = 0; o < NO; ++o) sacc[NO * k + o] = 0.0;
+    }
+    __syncthreads();
+    for (int base = e0; base < e1; base += blockDim.x) {
+        // neighbouring elements on different wavefronts, as in chunk_body
+        const int e = base + (int)blockDim.x <= e1
+                          ? base + (int)(threadIdx.x & 63) * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6)
+                          : base + (int)threadIdx.x;
+        if (e >= e1) break;
+        int lg[nn], lf[nn];
+#pragma unroll
+        for (int a = 0; a < nn; ++a) {
+            lg[a] = c.lg[(size_t)a * c.ld + e];
+            lf[a] = PERIODIC ? (int)c.lf[(size_t)a * c.ld + e] : lg[a];
+        }
+        double r[NO][nn];
+        element_project<T, GRAD>([&](int a, int i) { return sx[3 * lg[a] + i]; },
+                                 [&](int a, int i) { return sv[NI * lf[a] + i]; }, r);
+#pragma unroll
+        for (int a = 0; a < nn; ++a)
+#pragma unroll
+            for (int o = 0; o < NO; ++o) unsafeAtomicAdd(sacc + NO * lf[a] + o, r[o][a]);
+    }
+    __syncthreads();
+    // one thread per entry, so that the atomics of neighbouring lanes fall into the same cache lines
+    for (int t = threadIdx.x; t < NO * nf; t += blockDim.x) {
+        const int k = t / NO;
+        const uint32_t tag = (uint32_t)c.fnodes[f0 + k];
+        double *dst = out + NO * (size_t)(tag & ~kOwnedBit) + (t - NO * k);
+        if (tag & kOwnedBit) *dst = sacc[t];
+        else unsafeAtomicAdd(dst, sacc[t]);
+    }
+}
+
+template <bool GRAD, bool PERIODIC>
+__global__ __launch_bounds__(256) void k_project_chunks(ProjectView pv, const double *__restrict__ xyz,
+                                                        const double *__restrict__ in, double *__restrict__ out) {
+    extern __shared__ __align__(16) double lds[];
+    const int b = blockIdx.x;
+    auto chunk = [&](int k) { return xcd_block(b - pv.first[k], pv.first[k + 1] - pv.first[k]); };
+    if (b < pv.first[1]) project_chunk<LESASM_HEX08, GRAD, PERIODIC>(pv.v[0], chunk(0), lds, xyz, in, out);
+    else if (b < pv.first[2]) project_chunk<LESASM_PEN06, GRAD, PERIODIC>(pv.v[1], chunk(1), lds, xyz, in, out);
+    else if (b < pv.first[3]) project_chunk<LESASM_PYR05, GRAD, PERIODIC>(pv.v[2], chunk(2), lds, xyz, in, out);
+    else project_chunk<LESASM_TET04, GRAD, PERIODIC>(pv.v[3], chunk(3), lds, xyz, in, out);
+}
+
+// Adds the operator's contributions into the zeroed out (chunked meshes).
+template <bool GRAD>
+void launch_project_chunks(const lesasm_mesh *m, const double *in, double *out, hipStream_t s) {
+    static constexpr int kOrder[kNumCat] = {3, 2, 1, 0};  // HEX08, PEN06, PYR05, TET04: costliest chunks first
+    ProjectView pv{};
+    int doubles = 0;
+    bool periodic = false;
+    for (int i = 0; i < kNumCat; ++i) {
+        const Category &c = m->cat[kOrder[i]];
+        pv.v[i] = ChunkView{c.d_eoff, c.d_goff, c.d_gnodes, c.d_foff, c.d_fnodes, nullptr, c.d_lg, c.d_lf, c.d_delta,
+                            nullptr, (int32_t)c.n};
+        pv.first[i + 1] = pv.first[i] + c.n_chunks;
+        doubles = std::max(doubles, c.project_doubles);
+        periodic = periodic || c.d_lf != c.d_lg;
+    }
+    const dim3 grid(pv.first[kNumCat]), block(256);
+    const size_t shm = sizeof(double) * (size_t)doubles;
+    if (grid.x == 0) return;
+    if (periodic) hipLaunchKernelGGL((k_project_chunks<GRAD, true>), grid, block, shm, s, pv, m->d_xyz, in, out);
+    else hipLaunchKernelGGL((k_project_chunks<GRAD, false>), grid, block, shm, s, pv, m->d_xyz, in, out);
+}
+
 __device__ __forceinline__ int find_col(const int32_t *__restrict__ col, int lo, int hi, int key) {
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
@@ -711,7 +901,8 @@ extern "C" int lesasm_divergence(lesasm_mesh *m, const double *d_u, double *d_ou
     hipStream_t s = (hipStream_t)stream;
     if (!m->n_field) return LESASM_OK;
     hipLaunchKernelGGL(k_zero, dim3(grid_for(m->n_field, 256)), dim3(256), 0, s, d_out, (size_t)m->n_field);
-    LESASM_PER_CATEGORY(k_divergence, m, s, (const double *)m->d_xyz, d_u, d_out);
+    if (mesh_is_chunked(m)) launch_project_chunks<false>(m, d_u, d_out, s);
+    else LESASM_PER_CATEGORY(k_divergence, m, s, (const double *)m->d_xyz, d_u, d_out);
     LESASM_HIP_TRY(hipGetLastError());
     return LESASM_OK;
 }
@@ -722,7 +913,8 @@ extern "C" int lesasm_gradient(lesasm_mesh *m, const double *d_p, double *d_out,
     if (!m->n_field) return LESASM_OK;
     hipLaunchKernelGGL(k_zero, dim3(grid_for(3 * (size_t)m->n_field, 256)), dim3(256), 0, s, d_out,
                        3 * (size_t)m->n_field);
-    LESASM_PER_CATEGORY(k_gradient, m, s, (const double *)m->d_xyz, d_p, d_out);
+    if (mesh_is_chunked(m)) launch_project_chunks<true>(m, d_p, d_out, s);
+    else LESASM_PER_CATEGORY(k_gradient, m, s, (const double *)m->d_xyz, d_p, d_out);
     LESASM_HIP_TRY(hipGetLastError());
     return LESASM_OK;
 }
