@@ -386,78 +386,41 @@ __global__ __launch_bounds__(256) void k_laplacian(CatView c, const double *__re
 
 // ---- vector kernels ----------------------------------------------------------
 
-__global__ void k_spmv(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-                       const double *__restrict__ val, const double *__restrict__ x, double *__restrict__ y, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double s = 0.0;
-    for (int q = rowptr[i]; q < rowptr[i + 1]; ++q) s += val[q] * x[col[q]];
-    y[i] = s;
-}
-
-constexpr int kRedBlocks = 512;
-
-// Fixed-order two-level reduction: partial[b] = sum over a grid-stride slice.
-__global__ void k_dot_partial(const double *__restrict__ a, const double *__restrict__ b, int n,
-                              double *__restrict__ partial) {
-    __shared__ double sh[256];
-    double s = 0.0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        s += b ? a[i] * b[i] : a[i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[blockIdx.x] = sh[0];
-}
-
-__global__ void k_reduce_final(const double *__restrict__ partial, int nb, double *__restrict__ out) {
-    __shared__ double sh[kRedBlocks];
-    sh[threadIdx.x] = (int)threadIdx.x < nb ? partial[threadIdx.x] : 0.0;
-    __syncthreads();
-    for (int w = kRedBlocks / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = sh[0];
-}
-
-// Conjugate-gradient kernels.  A fixed grid (kCgBlocks x 256) walks the rows
-// in a fixed order, so every reduction is deterministic.  4096 blocks (16 per
-// CU) and four row entries in flight per lane keep enough loads outstanding
-// to hide the indirect gather's latency (on 1.76 M rows, 38 M nonzeros: 0.168
-// ms per iteration against 0.262 with 1024 blocks and one entry per lane).
-#ifndef LESASM_CG_BLOCKS
-#define LESASM_CG_BLOCKS 4096
-#endif
-#ifndef LESASM_CG_LANES
-#define LESASM_CG_LANES 8
-#endif
-#ifndef LESASM_CG_UNROLL
-#define LESASM_CG_UNROLL 4
-#endif
-constexpr int kCgBlocks = LESASM_CG_BLOCKS;
+// Conjugate-gradient kernels: three launches an iteration (product, residual
+// update, direction), each on a grid fixed by the row count, so every reduction
+// runs in a fixed order.  A kernel leaves one partial sum per workgroup; the
+// workgroups of the next one each add all of them, while their first rows are on
+// the way, instead of a single-workgroup reduction launch (5 us) between them.
+// An iteration with 2.9 k rows takes 15 us against 24 with five launches, with
+// 117 k rows 19 against 31, 0.45 M 37 against 55, 0.89 M 66 against 86, 8.8 M
+// (bound by the bytes) 667 against 676.
+constexpr int kSpmvBlocks = 8192;       // most workgroups (partial sums) of the product
+constexpr int kVecBlocks = 1024;        // and of the vector kernels
+constexpr int kVecRows = 2;             // rows a thread of the vector kernels has in flight
 constexpr int kMaxCapturedCg = 100000;  // CG iterations a step graph may hold
-constexpr int kLanesPerRow = LESASM_CG_LANES;
-constexpr int kRowUnroll = LESASM_CG_UNROLL;
+constexpr int kLanesPerRow = 8;         // CSR product: lanes per row
+constexpr int kRowUnroll = 4;           // and row entries in flight per lane
 
-// Captured CG iterations (the step graph): iteration `it` runs only while
-// it <= *state, where *state is the iteration that met the tolerance
-// (INT32_MAX until then).  Eager solves pass state = NULL.
+// CG iteration `it` runs only while it <= *state, where *state is the iteration
+// that met the tolerance (INT32_MAX until then).
 __device__ __forceinline__ bool cg_skip(const int *state, int it) { return state && it > *state; }
 
-// Fixed-order sum of one value per thread of a 256-thread block into out[0].
-__device__ __forceinline__ void block_sum_256(double v, double *sh, double *out) {
-    sh[threadIdx.x] = v;
+// Fixed-order sum of v over a workgroup of 256 threads, in every thread.
+__device__ __forceinline__ double block_sum_256(double v, double *sh) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    __syncthreads();  // sh may still be read from a previous sum
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = sh[0];
-    __syncthreads();
+    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+// Sum of partial[stride * b], b < nb, in every thread.
+__device__ __forceinline__ double partial_sum_256(const double *__restrict__ partial, int nb, int stride, double *sh) {
+    double v = 0.0;
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nb; b += 256) v += partial[(size_t)stride * b];
+    return block_sum_256(v, sh);
 }
 
 // q = K p with kLanesPerRow lanes per row (coalesced reads of the row's
@@ -466,23 +429,23 @@ __device__ __forceinline__ void block_sum_256(double v, double *sh, double *out)
 __global__ __launch_bounds__(256) void k_spmv_dot(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                                                   const double *__restrict__ val, const double *__restrict__ p,
                                                   double *__restrict__ q, int n, double *__restrict__ partial,
-                                                  const int *state = nullptr, int it = 0) {
+                                                  const int *state, int it) {
     if (cg_skip(state, it)) return;
-    __shared__ double sh[256];
+    __shared__ double sh[4];
     const int lane = threadIdx.x % kLanesPerRow;
     const int rows_per_block = 256 / kLanesPerRow;
     double pq = 0.0;
-    for (int base = blockIdx.x * rows_per_block; base < n; base += gridDim.x * rows_per_block) {
-        const int row = base + (int)threadIdx.x / kLanesPerRow;
+    for (int64_t base = blockIdx.x * rows_per_block; base < n; base += gridDim.x * rows_per_block) {
+        const int64_t row = base + (int)threadIdx.x / kLanesPerRow;
         double s = 0.0;
         if (row < n) {
             const int k1 = rowptr[row + 1];
-            for (int k = rowptr[row] + lane; k < k1; k += kRowUnroll * kLanesPerRow) {
+            for (int64_t k = rowptr[row] + lane; k < k1; k += kRowUnroll * kLanesPerRow) {
                 int c[kRowUnroll];
                 double v[kRowUnroll];
 #pragma unroll
                 for (int j = 0; j < kRowUnroll; ++j) {
-                    const int kk = k + j * kLanesPerRow;
+                    const int64_t kk = k + j * kLanesPerRow;
                     c[j] = kk < k1 ? col[kk] : -1;
                     v[j] = kk < k1 ? val[kk] : 0.0;
                 }
@@ -498,68 +461,97 @@ __global__ __launch_bounds__(256) void k_spmv_dot(const int32_t *__restrict__ ro
             pq += s * p[row];
         }
     }
-    block_sum_256(pq, sh, partial + blockIdx.x);
+    pq = block_sum_256(pq, sh);
+    if (threadIdx.x == 0) partial[blockIdx.x] = pq;
 }
 
 #ifndef LESASM_CG_SELL
 #define LESASM_CG_SELL 1
 #endif
 constexpr int kSlice = 64;  // rows per slice of the sliced-ELLPACK copy (one wavefront)
-#ifndef LESASM_SELL_UNROLL
-#define LESASM_SELL_UNROLL 4
-#endif
-#ifndef LESASM_SELL_NT
-#define LESASM_SELL_NT 1
-#endif
-constexpr int kSellUnroll = LESASM_SELL_UNROLL;  // row entries in flight per lane
-// the matrix is read once per SpMV: streamed past the caches when LESASM_SELL_NT
-template <class T> __device__ __forceinline__ T sell_load(const T *a) {
-    if (LESASM_SELL_NT) return __builtin_nontemporal_load(a);
-    return *a;
-}
+
+// Entries j .. j + U - 1 of a slice's 64 rows: columns and values.  The loads go
+// through a buffer descriptor of the slice's extent, so entries past its width
+// cost no branch and no traffic (they read as 0 and are not added).
+template <bool NT, int U> struct SellBatch {
+    int c[U];
+    double v[U];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t cols, __amdgpu_buffer_rsrc_t vals, unsigned lane, int j) {
+        constexpr int aux = NT ? 2 : 0;  // nontemporal
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            c[k] = (int)__builtin_amdgcn_raw_buffer_load_b32(cols, 4 * lane, 4 * kSlice * (j + k), aux);
+            v[k] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(vals, 8 * lane, 8 * kSlice * (j + k), aux));
+        }
+    }
+    __device__ __forceinline__ void gather(const double *__restrict__ p, double (&g)[U]) const {
+#pragma unroll
+        for (int k = 0; k < U; ++k) g[k] = p[(unsigned)c[k]];
+    }
+    __device__ __forceinline__ double add(double s, const double (&g)[U], int j, int w) const {
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const double t = fma(v[k], g[k], s);
+            s = j + k < w ? t : s;
+        }
+        return s;
+    }
+};
 
 // q = K p on the sliced-ELLPACK copy of K: slice s holds rows 64 s .. 64 s +
 // 63, padded to its longest row and stored column-major, so entry j of all 64
 // rows is one coalesced load; lane l adds row 64 s + l's entries in column
-// order (four in flight).  Padding entries hold value 0 and a valid column.
-// One wavefront per slice, slices in a fixed grid-stride order; partial[b] =
-// block sums of p.q.
+// order.  Padding entries hold value 0 and a valid column.  One wavefront per
+// slice, slices in a fixed grid-stride order; partial[b] = block sums of p.q.
+// Bound by the matrix bytes (12 B an entry) once enough loads are in flight:
+// U entries are loaded while the U before them gather p and are added.  U = 4
+// with plain loads (entries of 0.45 M rows: 24.0 us; 3, 6, 8: 25.0, 25.0, 26.2;
+// four at a time without the overlap 28.6), 3 with nontemporal ones (8.8 M rows:
+// 527 us; 2, 4, 6, 8: 546, 535, 551, 576; without the overlap 532).
+// NT: nontemporal matrix loads (see kKeepBytes).
+template <bool NT>
 __global__ __launch_bounds__(256) void k_spmv_sell_dot(const int32_t *__restrict__ soff,
                                                        const int32_t *__restrict__ scol,
                                                        const double *__restrict__ sval, const double *__restrict__ p,
                                                        double *__restrict__ q, int n, int nslices,
-                                                       double *__restrict__ partial, const int *state = nullptr,
-                                                       int it = 0) {
+                                                       double *__restrict__ partial, const int *state, int it) {
     if (cg_skip(state, it)) return;
-    __shared__ double sh[256];
-    const int lane = threadIdx.x % kSlice, wave = threadIdx.x / kSlice;
+    __shared__ double sh[4];
+    const unsigned lane = threadIdx.x % kSlice;
     const int waves = 256 / kSlice;
+    constexpr int U = NT ? 3 : 4;
     double pq = 0.0;
-    for (int sl = blockIdx.x * waves + wave; sl < nslices; sl += gridDim.x * waves) {
+    for (int sl = __builtin_amdgcn_readfirstlane(blockIdx.x * waves + threadIdx.x / kSlice); sl < nslices;
+         sl += gridDim.x * waves) {
         const int o0 = soff[sl], w = (soff[sl + 1] - o0) / kSlice;
-        const int32_t *cc = scol + o0 + lane;
-        const double *vv = sval + o0 + lane;
+        const auto cols = __builtin_amdgcn_make_buffer_rsrc((void *)(scol + o0), 0, 4 * kSlice * w, 0x00020000);
+        const auto vals = __builtin_amdgcn_make_buffer_rsrc((void *)(sval + o0), 0, 8 * kSlice * w, 0x00020000);
         double s = 0.0;
-        int j = 0;
-        for (; j + kSellUnroll <= w; j += kSellUnroll) {
-            int c[kSellUnroll];
-            double v[kSellUnroll];
-#pragma unroll
-            for (int k = 0; k < kSellUnroll; ++k) {
-                c[k] = sell_load(cc + kSlice * (j + k));
-                v[k] = sell_load(vv + kSlice * (j + k));
-            }
-#pragma unroll
-            for (int k = 0; k < kSellUnroll; ++k) s += v[k] * p[c[k]];
+        SellBatch<NT, U> a, b;
+        a.load(cols, vals, lane, 0);
+        // loads return in order: a batch's gathers are issued before the next
+        // batch's loads, so that adding them does not wait for those
+        for (int j = 0; j < w; j += 2 * U) {
+            double g[U];
+            a.gather(p, g);
+            __builtin_amdgcn_sched_barrier(0);
+            b.load(cols, vals, lane, j + U);
+            __builtin_amdgcn_sched_barrier(0);
+            s = a.add(s, g, j, w);
+            b.gather(p, g);
+            __builtin_amdgcn_sched_barrier(0);
+            a.load(cols, vals, lane, j + 2 * U);
+            __builtin_amdgcn_sched_barrier(0);
+            s = b.add(s, g, j + U, w);
         }
-        for (; j < w; ++j) s += sell_load(vv + kSlice * j) * p[sell_load(cc + kSlice * j)];
-        const int row = sl * kSlice + lane;
+        const int row = sl * kSlice + (int)lane;
         if (row < n) {
             q[row] = s;
             pq += s * p[row];
         }
     }
-    block_sum_256(pq, sh, partial + blockIdx.x);
+    pq = block_sum_256(pq, sh);
+    if (threadIdx.x == 0) partial[blockIdx.x] = pq;
 }
 
 // sliced-ELLPACK values from the assembled CSR values (src < 0: padding)
@@ -569,66 +561,111 @@ __global__ void k_sell_fill(const int32_t *__restrict__ src, const double *__res
         sval[i] = src[i] >= 0 ? val[src[i]] : 0.0;
 }
 
+// pq = sum of the product's nb partial sums (kept in scal[i_pq]);
 // alpha = rz / pq;  r -= alpha q;  z = r / diag  (x is advanced with the old
 // direction by k_cg_direction, which reads p anyway);
 // partial[2b] = block sums of r.z, partial[2b+1] = of r.r
 __global__ __launch_bounds__(256) void k_cg_update(double *__restrict__ r, double *__restrict__ z,
                                                    const double *__restrict__ q, const double *__restrict__ diag,
-                                                   const double *__restrict__ scal, int i_rz, int i_pq, int n,
-                                                   double *__restrict__ partial, const int *state = nullptr,
-                                                   int it = 0) {
+                                                   double *scal, int i_rz, int i_pq, int n,
+                                                   const double *__restrict__ pq_partial, int nb,
+                                                   double *__restrict__ partial, const int *state, int it) {
     if (cg_skip(state, it)) return;
-    __shared__ double sh[256];
-    const double alpha = scal[i_rz] / scal[i_pq];
+    __shared__ double sh[4];
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    int64_t i = blockIdx.x * 256 + threadIdx.x;
+    // rows i, i + stride, ... kVecRows at a time; the first ones are loaded
+    // before the partial sums are waited for
+    double rv[kVecRows], qv[kVecRows], dv[kVecRows];
+    auto load = [&](int64_t at) {
+#pragma unroll
+        for (int k = 0; k < kVecRows; ++k)
+            if (at + k * stride < n) {
+                rv[k] = r[at + k * stride];
+                qv[k] = q[at + k * stride];
+                dv[k] = diag[at + k * stride];
+            }
+    };
+    load(i);
+    const double pq = partial_sum_256(pq_partial, nb, 1, sh);
+    if (blockIdx.x == 0 && threadIdx.x == 0) scal[i_pq] = pq;
+    const double alpha = scal[i_rz] / pq;
     double rz = 0.0, rr = 0.0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const double ri = r[i] - alpha * q[i];
-        const double zi = ri / diag[i];
-        r[i] = ri;
-        z[i] = zi;
-        rz += ri * zi;
-        rr += ri * ri;
+    while (i < n) {
+#pragma unroll
+        for (int k = 0; k < kVecRows; ++k)
+            if (i + k * stride < n) {
+                const double ri = rv[k] - alpha * qv[k];
+                const double zi = ri / dv[k];
+                r[i + k * stride] = ri;
+                z[i + k * stride] = zi;
+                rz += ri * zi;
+                rr += ri * ri;
+            }
+        i += kVecRows * stride;
+        load(i);
     }
-    block_sum_256(rz, sh, partial + 2 * blockIdx.x);
-    block_sum_256(rr, sh, partial + 2 * blockIdx.x + 1);
+    rz = block_sum_256(rz, sh);
+    rr = block_sum_256(rr, sh);
+    if (threadIdx.x == 0) {
+        partial[2 * blockIdx.x] = rz;
+        partial[2 * blockIdx.x + 1] = rr;
+    }
 }
 
-// out[j] = fixed-order sum of partial[stride * b + j] over b < nb, for j < m
-// (one 1024-thread block).  In a captured CG with conv set, iteration `it`
-// that brings out1 (r.r) to at most tol2 * (*bb) records itself in *state.
-__global__ __launch_bounds__(1024) void k_reduce_strided(const double *__restrict__ partial, int nb, int stride,
-                                                         int m, double *__restrict__ out0, double *__restrict__ out1,
-                                                         int *state = nullptr, int it = 0, bool conv = false,
-                                                         const double *bb = nullptr, double tol2 = 0.0) {
-    if (cg_skip(state, it)) return;
-    __shared__ double sh[1024];
-    for (int j = 0; j < m; ++j) {
-        double v = 0.0;
-        for (int b = threadIdx.x; b < nb; b += blockDim.x) v += partial[stride * b + j];
-        sh[threadIdx.x] = v;
-        __syncthreads();
-        for (int w = 512; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) *(j == 0 ? out0 : out1) = sh[0];
-        __syncthreads();
-    }
-    if (conv && threadIdx.x == 0 && *out1 <= tol2 * *bb) *state = it;
-}
-
-// x += (rz_old / pq) p;  p = z + (rz_new / rz_old) p
+// rz_new = sum of the update's nb partial sums (kept in scal[i_new]);
+// x += (rz_old / pq) p;  p = z + (rz_new / rz_old) p.
+// With test set, r.r (kept in scal[i_rr]) is compared with the tolerance and an
+// iteration that meets it records itself in *state: rr <= tol2 bb.
 __global__ __launch_bounds__(256) void k_cg_direction(double *__restrict__ x, double *__restrict__ p,
-                                                      const double *__restrict__ z, const double *__restrict__ scal,
-                                                      int i_new, int i_old, int i_pq, int n,
-                                                      const int *state = nullptr, int it = 0) {
+                                                      const double *__restrict__ z, double *scal, int i_new, int i_old,
+                                                      int i_pq, int i_rr, int i_bb, int n,
+                                                      const double *__restrict__ partial, int nb, int *state, int it,
+                                                      bool test, double rtol, double *host) {
     if (cg_skip(state, it)) return;
+    __shared__ double sh[4];
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    int64_t i = blockIdx.x * 256 + threadIdx.x;
+    double xv[kVecRows], pv[kVecRows], zv[kVecRows];
+    auto load = [&](int64_t at) {  // as in k_cg_update
+#pragma unroll
+        for (int k = 0; k < kVecRows; ++k)
+            if (at + k * stride < n) {
+                xv[k] = x[at + k * stride];
+                pv[k] = p[at + k * stride];
+                zv[k] = z[at + k * stride];
+            }
+    };
+    load(i);
+    const double rz = partial_sum_256(partial, nb, 2, sh);
+    if (blockIdx.x == 0) {  // (its own workgroup's other work does not depend on these)
+        const double rr = test ? partial_sum_256(partial + 1, nb, 2, sh) : 0.0;
+        if (threadIdx.x == 0) {
+            scal[i_new] = rz;
+            if (test) {
+                const double bb = scal[i_bb];
+                const bool met = sqrt(rr) <= rtol * sqrt(bb);
+                scal[i_rr] = rr;
+                if (met) *state = it;
+                if (host) {
+                    host[0] = rr;
+                    host[1] = bb;
+                    host[2] = met ? 1.0 : 0.0;
+                }
+            }
+        }
+    }
     const double alpha = scal[i_old] / scal[i_pq];
-    const double beta = scal[i_new] / scal[i_old];
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const double pi = p[i];
-        x[i] += alpha * pi;
-        p[i] = z[i] + beta * pi;
+    const double beta = rz / scal[i_old];
+    while (i < n) {
+#pragma unroll
+        for (int k = 0; k < kVecRows; ++k)
+            if (i + k * stride < n) {
+                x[i + k * stride] = xv[k] + alpha * pv[k];
+                p[i + k * stride] = zv[k] + beta * pv[k];
+            }
+        i += kVecRows * stride;
+        load(i);
     }
 }
 
@@ -641,31 +678,6 @@ __global__ void k_lincomb(double *__restrict__ y, double a0, const double *__res
         if (x2) v += a2 * x2[i];
         y[i] = v;
     }
-}
-
-// y[i] += alpha * x[i] with alpha = scale * (*num) / (*den), read on the device
-__global__ void k_axpy_ratio(double *__restrict__ y, const double *__restrict__ x, const double *num,
-                             const double *den, double scale, int n) {
-    const double alpha = scale * (*num) / (*den);
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) y[i] += alpha * x[i];
-}
-
-// p = z + (num/den) p
-__global__ void k_xpby_ratio(double *__restrict__ p, const double *__restrict__ z, const double *num,
-                             const double *den, int n) {
-    const double beta = (*num) / (*den);
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = z[i] + beta * p[i];
-}
-
-// z = x / d (Jacobi)
-__global__ void k_jacobi(double *__restrict__ z, const double *__restrict__ x, const double *__restrict__ d, int n) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) z[i] = x[i] / d[i];
-}
-
-// x -= (*sum) / n
-__global__ void k_sub_mean(double *__restrict__ x, const double *sum, int n) {
-    const double m = (*sum) / n;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) x[i] -= m;
 }
 
 __global__ void k_diag(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
@@ -689,10 +701,60 @@ __global__ void k_correct(double *__restrict__ u, const double *__restrict__ ust
     }
 }
 
-// Start of a captured CG: no iteration yet met the tolerance; with a zero
-// right-hand side every iteration is skipped.
-__global__ void k_cg_begin(int *state, const double *bb) {
-    if (threadIdx.x == 0) state[0] = *bb > 0.0 ? INT32_MAX : 0;
+// Block sums of a (the first of two passes that take a mean).
+__global__ __launch_bounds__(256) void k_sum_partial(const double *__restrict__ a, int n, double *__restrict__ partial) {
+    __shared__ double sh[4];
+    double v = 0.0;
+#pragma unroll 4
+    for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) v += a[i];
+    v = block_sum_256(v, sh);
+    if (threadIdx.x == 0) partial[blockIdx.x] = v;
+}
+
+// x -= mean(x), from the block sums of x
+__global__ __launch_bounds__(256) void k_sub_mean(double *__restrict__ x, const double *__restrict__ partial, int nb, int n) {
+    __shared__ double sh[4];
+    const double m = partial_sum_256(partial, nb, 1, sh) / n;
+    for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) x[i] -= m;
+}
+
+// Start of a CG from the block sums of b: r = b - mean(b), x = 0, z = r / diag,
+// p = z; out[2k], out[2k+1] = block sums of r.r (= b.b) and r.z.  x may be b.
+__global__ __launch_bounds__(256) void k_cg_setup(const double *b, const double *__restrict__ diag,
+                                                  double *x, double *__restrict__ r, double *__restrict__ z,
+                                                  double *__restrict__ p, int n,
+                                                  const double *__restrict__ partial, int nb, double *__restrict__ out) {
+    __shared__ double sh[4];
+    const double m = partial_sum_256(partial, nb, 1, sh) / n;
+    double bb = 0.0, rz = 0.0;
+    for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const double ri = b[i] - m, zi = ri / diag[i];
+        x[i] = 0.0;
+        r[i] = ri;
+        z[i] = zi;
+        p[i] = zi;
+        bb += ri * ri;
+        rz += ri * zi;
+    }
+    bb = block_sum_256(bb, sh);
+    rz = block_sum_256(rz, sh);
+    if (threadIdx.x == 0) {
+        out[2 * blockIdx.x] = bb;
+        out[2 * blockIdx.x + 1] = rz;
+    }
+}
+
+// b.b and r.z of the start, and *state: no iteration yet met the tolerance;
+// with a zero right-hand side every iteration is skipped.
+__global__ __launch_bounds__(256) void k_cg_begin(const double *__restrict__ partial, int nb, double *scal, int i_bb,
+                                                  int i_rz, int *state) {
+    __shared__ double sh[4];
+    const double bb = partial_sum_256(partial, nb, 2, sh), rz = partial_sum_256(partial + 1, nb, 2, sh);
+    if (threadIdx.x == 0) {
+        scal[i_bb] = bb;
+        scal[i_rz] = rz;
+        state[0] = bb > 0.0 ? INT32_MAX : 0;
+    }
 }
 
 // End of a captured CG: rec = {iterations run, relative residual, converged}.
@@ -737,9 +799,10 @@ struct lesasm_stepper {
     int32_t *rowptr = nullptr, *col = nullptr;
     double *val = nullptr, *diag = nullptr;
     double *k1 = nullptr, *k3 = nullptr, *us = nullptr, *ustar = nullptr, *gdp = nullptr;  // [n][3]
-    double *b = nullptr, *x = nullptr, *r = nullptr, *z = nullptr, *pv = nullptr, *q = nullptr;  // [n]
+    double *x = nullptr, *r = nullptr, *z = nullptr, *pv = nullptr, *q = nullptr;  // [n]
     double *partial = nullptr, *scal = nullptr;  // reductions
     std::vector<void *> allocs;
+    int spmv_blocks = 0, vec_blocks = 0;  // grids of the CG kernels
     int last_iters = 0;
     double last_res = 0.0;
     int64_t nnz = 0;
@@ -748,7 +811,9 @@ struct lesasm_stepper {
     double *sval = nullptr;
     int nslices = 0;
     int64_t sell_entries = 0;
-    int *d_cgstate = nullptr;   // captured CG: iteration that met the tolerance
+    int *d_cgstate = nullptr;   // iteration that met the tolerance (see cg_skip)
+    double *h_rec = nullptr;    // pinned: the last convergence test, {r.r, b.b, met}
+    hipEvent_t ev_check = nullptr;  // end of the iteration that made it
 };
 
 // A whole time step captured in a HIP graph, bound to one (u, p) pair.
@@ -780,116 +845,115 @@ void stepper_free(lesasm_stepper *st) {
     if (!st) return;
     (void)hipDeviceSynchronize();
     for (void *p : st->allocs) device_free(p);
+    if (st->h_rec) (void)hipHostFree(st->h_rec);
+    if (st->ev_check) (void)hipEventDestroy(st->ev_check);
     delete st;
 }
 
-enum { S_RZ = 0, S_PQ, S_RR, S_RZN, S_BB, S_SUM, S_NUM };
+enum { S_RZ = 0, S_PQ, S_RR, S_RZN, S_BB, S_NUM };
 
-int dot(lesasm_stepper *st, const double *a, const double *b, int which, hipStream_t s) {
-    hipLaunchKernelGGL(k_dot_partial, dim3(kRedBlocks), dim3(256), 0, s, a, b, st->n, st->partial);
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kRedBlocks), 0, s, st->partial, kRedBlocks, st->scal + which);
-    return LESASM_OK;
+// A matrix copy up to this size stays in the 256 MB Infinity Cache between
+// products; a larger one is read past it (nontemporal), so that p and the other
+// vectors keep the caches.  Per iteration, plain against nontemporal: 122 MB 41
+// against 51 us, 242 MB 72 against 82, 476 MB 157 against 150.
+constexpr int64_t kKeepBytes = (int64_t)320 << 20;
+
+void launch_spmv(const lesasm_stepper *st, const double *p, double *q, const int *state, int it, hipStream_t s) {
+    const dim3 g(st->spmv_blocks), b(256);
+    if (!st->sval)
+        hipLaunchKernelGGL(k_spmv_dot, g, b, 0, s, st->rowptr, st->col, st->val, p, q, st->n, st->partial, state, it);
+    else if (12 * st->sell_entries > kKeepBytes)
+        hipLaunchKernelGGL(k_spmv_sell_dot<true>, g, b, 0, s, st->soff, st->scol, st->sval, p, q, st->n, st->nslices,
+                           st->partial, state, it);
+    else
+        hipLaunchKernelGGL(k_spmv_sell_dot<false>, g, b, 0, s, st->soff, st->scol, st->sval, p, q, st->n, st->nslices,
+                           st->partial, state, it);
 }
 
+// CG iteration it (1, 2, ...) for solution x.  The old and new r.z use two slots
+// alternately, so that no scalar is overwritten while a kernel may still read it.
+void launch_cg_iteration(lesasm_stepper *st, double *x, int it, bool test, double *host, hipStream_t s) {
+    const int i_rz = it & 1 ? S_RZ : S_RZN, i_rzn = it & 1 ? S_RZN : S_RZ;
+    int *state = st->d_cgstate;
+    const dim3 g(st->vec_blocks), b(256);
+    double *rpart = st->partial + kSpmvBlocks;
+    launch_spmv(st, st->pv, st->q, state, it, s);
+    hipLaunchKernelGGL(k_cg_update, g, b, 0, s, st->r, st->z, st->q, st->diag, st->scal, i_rz, (int)S_PQ, st->n,
+                       st->partial, st->spmv_blocks, rpart, (const int *)state, it);
+    hipLaunchKernelGGL(k_cg_direction, g, b, 0, s, x, st->pv, st->z, st->scal, i_rzn, i_rz, (int)S_PQ, (int)S_RR,
+                       (int)S_BB, st->n, rpart, st->vec_blocks, state, it, test, st->rtol, host);
+}
+
+// Start of a solve (before iteration 1) and its end (x to zero mean).
+void launch_cg_start(lesasm_stepper *st, const double *b_in, double *x, hipStream_t s) {
+    const dim3 g(st->vec_blocks), b(256);
+    double *rpart = st->partial + kSpmvBlocks;
+    hipLaunchKernelGGL(k_sum_partial, g, b, 0, s, b_in, st->n, st->partial);
+    hipLaunchKernelGGL(k_cg_setup, g, b, 0, s, b_in, st->diag, x, st->r, st->z, st->pv, st->n, st->partial,
+                       st->vec_blocks, rpart);
+    hipLaunchKernelGGL(k_cg_begin, dim3(1), b, 0, s, rpart, st->vec_blocks, st->scal, (int)S_BB, (int)S_RZ,
+                       st->d_cgstate);
+}
+
+void launch_cg_finish(lesasm_stepper *st, double *x, hipStream_t s) {
+    const dim3 g(st->vec_blocks), b(256);
+    hipLaunchKernelGGL(k_sum_partial, g, b, 0, s, x, st->n, st->partial);
+    hipLaunchKernelGGL(k_sub_mean, g, b, 0, s, x, st->partial, st->vec_blocks, st->n);
+}
+
+// The convergence test runs on the device every check_every iterations (and
+// after the last) and tells the host through pinned memory.  The host queues
+// kCgAhead iterations behind a test before it waits for it, so the GPU does not
+// idle while the answer travels (0.45 M rows: 36.9 against 38.8 us an iteration
+// with a copy and a wait); if the test was met they return at once.
+constexpr int kCgAhead = 4;
+
 int pressure_solve(lesasm_stepper *st, const double *b_in, double *x, hipStream_t s) {
-    const int n = st->n;
-    const int g = grid_for(n, 256);
-    // b = b_in - mean(b_in)
-    LESASM_HIP_TRY(hipMemcpyAsync(st->b, b_in, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-    dot(st, st->b, nullptr, S_SUM, s);
-    hipLaunchKernelGGL(k_sub_mean, dim3(g), dim3(256), 0, s, st->b, st->scal + S_SUM, n);
-    dot(st, st->b, st->b, S_BB, s);
-    hipLaunchKernelGGL(k_zero, dim3(g), dim3(256), 0, s, x, (size_t)n);
-    LESASM_HIP_TRY(hipMemcpyAsync(st->r, st->b, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-    hipLaunchKernelGGL(k_jacobi, dim3(g), dim3(256), 0, s, st->z, st->r, st->diag, n);
-    LESASM_HIP_TRY(hipMemcpyAsync(st->pv, st->z, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-    dot(st, st->r, st->z, S_RZ, s);
-    double host[S_NUM] = {0};
-    LESASM_HIP_TRY(hipMemcpyAsync(host, st->scal, sizeof(host), hipMemcpyDeviceToHost, s));
-    LESASM_HIP_TRY(hipStreamSynchronize(s));
-    const double bnorm = std::sqrt(host[S_BB]);
-    int it = 0;
-    double res = bnorm;
-    if (bnorm > 0.0) {
-        // rz lives in two slots used alternately, so no scalar is overwritten
-        // while a kernel may still read it.
-        int i_rz = S_RZ, i_rzn = S_RZN;
-        for (it = 1; it <= st->maxit; ++it) {
-            if (st->sval)
-                hipLaunchKernelGGL(k_spmv_sell_dot, dim3(kCgBlocks), dim3(256), 0, s, st->soff, st->scol, st->sval,
-                                   st->pv, st->q, n, st->nslices, st->partial);
-            else
-                hipLaunchKernelGGL(k_spmv_dot, dim3(kCgBlocks), dim3(256), 0, s, st->rowptr, st->col, st->val, st->pv,
-                                   st->q, n, st->partial);
-            hipLaunchKernelGGL(k_reduce_strided, dim3(1), dim3(1024), 0, s, st->partial, kCgBlocks, 1, 1,
-                               st->scal + S_PQ, st->scal + S_PQ);
-            hipLaunchKernelGGL(k_cg_update, dim3(kCgBlocks), dim3(256), 0, s, st->r, st->z, st->q, st->diag,
-                               st->scal, i_rz, S_PQ, n, st->partial);
-            hipLaunchKernelGGL(k_reduce_strided, dim3(1), dim3(1024), 0, s, st->partial, kCgBlocks, 2, 2,
-                               st->scal + i_rzn, st->scal + S_RR);
-            hipLaunchKernelGGL(k_cg_direction, dim3(kCgBlocks), dim3(256), 0, s, x, st->pv, st->z, st->scal, i_rzn,
-                               i_rz, S_PQ, n);
-            std::swap(i_rz, i_rzn);
-            if (it % st->check_every == 0 || it == st->maxit) {
-                LESASM_HIP_TRY(hipMemcpyAsync(host, st->scal, sizeof(host), hipMemcpyDeviceToHost, s));
-                LESASM_HIP_TRY(hipStreamSynchronize(s));
-                res = std::sqrt(host[S_RR]);
-                if (res <= st->rtol * bnorm) break;
-            }
+    launch_cg_start(st, b_in, x, s);
+    int queued = 0, at = 0;
+    double res = 0.0;
+    bool met = false;
+    while (at < st->maxit && !met) {
+        at = std::min(at + st->check_every, st->maxit);
+        const int next = std::min(at + st->check_every, st->maxit);
+        st->h_rec[2] = -1.0;
+        while (queued < at) {
+            ++queued;
+            launch_cg_iteration(st, x, queued, queued == at, queued == at ? st->h_rec : nullptr, s);
         }
+        LESASM_HIP_TRY(hipEventRecord(st->ev_check, s));
+        while (queued < std::min(at + kCgAhead, next - 1)) {
+            ++queued;
+            launch_cg_iteration(st, x, queued, false, nullptr, s);
+        }
+        LESASM_HIP_TRY(hipGetLastError());
+        LESASM_HIP_TRY(hipEventSynchronize(st->ev_check));
+        const volatile double *rec = st->h_rec;
+        if (rec[2] < 0.0) {  // skipped: zero right-hand side, x = 0
+            at = 0;
+            break;
+        }
+        res = std::sqrt(rec[0]) / std::sqrt(rec[1]);
+        met = rec[2] > 0.0;
     }
-    st->last_iters = std::min(it, st->maxit);
-    st->last_res = bnorm > 0.0 ? res / bnorm : 0.0;
-    dot(st, x, nullptr, S_SUM, s);
-    hipLaunchKernelGGL(k_sub_mean, dim3(g), dim3(256), 0, s, x, st->scal + S_SUM, n);
+    st->last_iters = at;
+    st->last_res = res;
+    launch_cg_finish(st, x, s);
     LESASM_HIP_TRY(hipGetLastError());
     return LESASM_OK;
 }
 
-// The same solve for graph capture: no host reads and no copies through the
-// copy engine.  Exactly cg_iters iterations are captured; once the residual
-// meets the tolerance (tested after every iteration, on the device) the
-// remaining iterations return at once.  rec receives the iteration count,
-// relative residual and convergence flag.
+// The same solve for graph capture, without host reads.  Exactly cg_iters
+// iterations are captured; once the residual meets the tolerance (tested after
+// every iteration) the remaining iterations return at once.  rec receives the
+// iteration count, relative residual and convergence flag.
 int pressure_solve_captured(lesasm_stepper *st, const double *b_in, double *x, hipStream_t s, int cg_iters,
                             double *rec) {
-    const int n = st->n;
-    const int g = grid_for(n, 256);
-    hipLaunchKernelGGL(k_lincomb, dim3(g), dim3(256), 0, s, st->b, 1.0, b_in, 0.0, nullptr, 0.0, nullptr, (size_t)n);
-    dot(st, st->b, nullptr, S_SUM, s);
-    hipLaunchKernelGGL(k_sub_mean, dim3(g), dim3(256), 0, s, st->b, st->scal + S_SUM, n);
-    dot(st, st->b, st->b, S_BB, s);
-    hipLaunchKernelGGL(k_zero, dim3(g), dim3(256), 0, s, x, (size_t)n);
-    hipLaunchKernelGGL(k_lincomb, dim3(g), dim3(256), 0, s, st->r, 1.0, st->b, 0.0, nullptr, 0.0, nullptr, (size_t)n);
-    hipLaunchKernelGGL(k_jacobi, dim3(g), dim3(256), 0, s, st->z, st->r, st->diag, n);
-    hipLaunchKernelGGL(k_lincomb, dim3(g), dim3(256), 0, s, st->pv, 1.0, st->z, 0.0, nullptr, 0.0, nullptr, (size_t)n);
-    dot(st, st->r, st->z, S_RZ, s);
-    hipLaunchKernelGGL(k_cg_begin, dim3(1), dim3(64), 0, s, st->d_cgstate, st->scal + S_BB);
-    const double tol2 = st->rtol * st->rtol;
-    int i_rz = S_RZ, i_rzn = S_RZN;
-    int *state = st->d_cgstate;
-    for (int it = 1; it <= cg_iters; ++it) {
-        if (st->sval)
-            hipLaunchKernelGGL(k_spmv_sell_dot, dim3(kCgBlocks), dim3(256), 0, s, st->soff, st->scol, st->sval, st->pv,
-                               st->q, n, st->nslices, st->partial, (const int *)state, it);
-        else
-            hipLaunchKernelGGL(k_spmv_dot, dim3(kCgBlocks), dim3(256), 0, s, st->rowptr, st->col, st->val, st->pv,
-                               st->q, n, st->partial, (const int *)state, it);
-        hipLaunchKernelGGL(k_reduce_strided, dim3(1), dim3(1024), 0, s, st->partial, kCgBlocks, 1, 1,
-                           st->scal + S_PQ, st->scal + S_PQ, state, it, false, (const double *)nullptr, 0.0);
-        hipLaunchKernelGGL(k_cg_update, dim3(kCgBlocks), dim3(256), 0, s, st->r, st->z, st->q, st->diag, st->scal,
-                           i_rz, S_PQ, n, st->partial, (const int *)state, it);
-        hipLaunchKernelGGL(k_reduce_strided, dim3(1), dim3(1024), 0, s, st->partial, kCgBlocks, 2, 2,
-                           st->scal + i_rzn, st->scal + S_RR, state, it, true, (const double *)(st->scal + S_BB),
-                           tol2);
-        hipLaunchKernelGGL(k_cg_direction, dim3(kCgBlocks), dim3(256), 0, s, x, st->pv, st->z, st->scal, i_rzn, i_rz,
-                           S_PQ, n, (const int *)state, it);
-        std::swap(i_rz, i_rzn);
-    }
-    hipLaunchKernelGGL(k_cg_end, dim3(1), dim3(64), 0, s, (const int *)state, (const double *)st->scal, (int)S_RR,
-                       (int)S_BB, cg_iters, rec);
-    dot(st, x, nullptr, S_SUM, s);
-    hipLaunchKernelGGL(k_sub_mean, dim3(g), dim3(256), 0, s, x, st->scal + S_SUM, n);
+    launch_cg_start(st, b_in, x, s);
+    for (int it = 1; it <= cg_iters; ++it) launch_cg_iteration(st, x, it, true, nullptr, s);
+    hipLaunchKernelGGL(k_cg_end, dim3(1), dim3(64), 0, s, (const int *)st->d_cgstate, (const double *)st->scal,
+                       (int)S_RR, (int)S_BB, cg_iters, rec);
+    launch_cg_finish(st, x, s);
     LESASM_HIP_TRY(hipGetLastError());
     return LESASM_OK;
 }
@@ -940,6 +1004,8 @@ extern "C" int lesasm_stepper_create(lesasm_mesh *m, double nu, double dt, doubl
     st->maxit = maxit;
     st->n = (int)m->n_field;
     const int n = st->n;
+    st->spmv_blocks = std::max(1, std::min((int)(((int64_t)n + 4 * kSlice - 1) / (4 * kSlice)), kSpmvBlocks));
+    st->vec_blocks = std::max(1, std::min((int)(((int64_t)n + 255) / 256), kVecBlocks));
 
     // CSR pattern of K: for each field node, the field nodes of its elements
     std::vector<int32_t> ninc(n + 1, 0);
@@ -984,12 +1050,13 @@ extern "C" int lesasm_stepper_create(lesasm_mesh *m, double nu, double dt, doubl
         (rc = salloc(st, &st->val, col.size())) || (rc = salloc(st, &st->diag, (size_t)n)) ||
         (rc = salloc(st, &st->k1, 3 * (size_t)n)) || (rc = salloc(st, &st->k3, 3 * (size_t)n)) ||
         (rc = salloc(st, &st->us, 3 * (size_t)n)) || (rc = salloc(st, &st->ustar, 3 * (size_t)n)) ||
-        (rc = salloc(st, &st->gdp, 3 * (size_t)n)) || (rc = salloc(st, &st->b, (size_t)n)) ||
-        (rc = salloc(st, &st->x, (size_t)n)) || (rc = salloc(st, &st->r, (size_t)n)) ||
+        (rc = salloc(st, &st->gdp, 3 * (size_t)n)) || (rc = salloc(st, &st->x, (size_t)n)) || (rc = salloc(st, &st->r, (size_t)n)) ||
         (rc = salloc(st, &st->z, (size_t)n)) || (rc = salloc(st, &st->pv, (size_t)n)) ||
-        (rc = salloc(st, &st->q, (size_t)n)) || (rc = salloc(st, &st->partial, 2 * kCgBlocks)) ||
+        (rc = salloc(st, &st->q, (size_t)n)) || (rc = salloc(st, &st->partial, kSpmvBlocks + 2 * kVecBlocks)) ||
         (rc = salloc(st, &st->scal, S_NUM)) || (rc = salloc(st, &st->d_cgstate, 4)))
         return rc;
+    LESASM_HIP_TRY(hipHostMalloc((void **)&st->h_rec, 4 * sizeof(double), hipHostMallocCoherent));
+    LESASM_HIP_TRY(hipEventCreateWithFlags(&st->ev_check, hipEventDisableTiming));
     if (n) {
         LESASM_HIP_TRY(hipMemcpy(st->rowptr, rowptr.data(), sizeof(int32_t) * rowptr.size(), hipMemcpyHostToDevice));
         LESASM_HIP_TRY(hipMemcpy(st->col, col.data(), sizeof(int32_t) * col.size(), hipMemcpyHostToDevice));
@@ -1072,12 +1139,7 @@ extern "C" int lesasm_stepper_spmv(lesasm_stepper *st, const double *d_p, double
     if (d_p == d_q) return fail(LESASM_E_INVALID_ARG, "stepper_spmv: p and q must not alias");
     if (!st->n) return LESASM_OK;
     hipStream_t s = (hipStream_t)stream;
-    if (st->sval)
-        hipLaunchKernelGGL(k_spmv_sell_dot, dim3(kCgBlocks), dim3(256), 0, s, st->soff, st->scol, st->sval, d_p, d_q,
-                           st->n, st->nslices, st->partial);
-    else
-        hipLaunchKernelGGL(k_spmv_dot, dim3(kCgBlocks), dim3(256), 0, s, st->rowptr, st->col, st->val, d_p, d_q,
-                           st->n, st->partial);
+    launch_spmv(st, d_p, d_q, nullptr, 0, s);
     LESASM_HIP_TRY(hipGetLastError());
     return LESASM_OK;
 }
