@@ -415,12 +415,39 @@ __device__ __forceinline__ double block_sum_256(double v, double *sh) {
     return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// Sum of partial[stride * b], b < nb, in every thread.
-__device__ __forceinline__ double partial_sum_256(const double *__restrict__ partial, int nb, int stride, double *sh) {
+// The same of two values at once (sh: 8 doubles).
+__device__ __forceinline__ void block_sum2_256(double &v, double &w, double *sh) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        v += __shfl_xor(v, o);
+        w += __shfl_xor(w, o);
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        sh[threadIdx.x >> 6] = v;
+        sh[4 + (threadIdx.x >> 6)] = w;
+    }
+    __syncthreads();
+    v = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    w = (sh[4] + sh[5]) + (sh[6] + sh[7]);
+}
+
+// Sum of partial[b], b < nb, in every thread; and of pairs partial[2b], partial[2b+1].
+__device__ __forceinline__ double partial_sum_256(const double *__restrict__ partial, int nb, double *sh) {
     double v = 0.0;
 #pragma unroll 4
-    for (int b = threadIdx.x; b < nb; b += 256) v += partial[(size_t)stride * b];
+    for (int b = threadIdx.x; b < nb; b += 256) v += partial[b];
     return block_sum_256(v, sh);
+}
+__device__ __forceinline__ void partial_sum2_256(const double *__restrict__ partial, int nb, double &v, double &w,
+                                                 double *sh) {
+    v = w = 0.0;
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nb; b += 256) {
+        v += partial[2 * b];
+        w += partial[2 * b + 1];
+    }
+    block_sum2_256(v, w, sh);
 }
 
 // q = K p with kLanesPerRow lanes per row (coalesced reads of the row's
@@ -571,7 +598,7 @@ __global__ __launch_bounds__(256) void k_cg_update(double *__restrict__ r, doubl
                                                    const double *__restrict__ pq_partial, int nb,
                                                    double *__restrict__ partial, const int *state, int it) {
     if (cg_skip(state, it)) return;
-    __shared__ double sh[4];
+    __shared__ double sh[8];
     const int64_t stride = (int64_t)gridDim.x * 256;
     int64_t i = blockIdx.x * 256 + threadIdx.x;
     // rows i, i + stride, ... kVecRows at a time; the first ones are loaded
@@ -587,7 +614,7 @@ __global__ __launch_bounds__(256) void k_cg_update(double *__restrict__ r, doubl
             }
     };
     load(i);
-    const double pq = partial_sum_256(pq_partial, nb, 1, sh);
+    const double pq = partial_sum_256(pq_partial, nb, sh);
     if (blockIdx.x == 0 && threadIdx.x == 0) scal[i_pq] = pq;
     const double alpha = scal[i_rz] / pq;
     double rz = 0.0, rr = 0.0;
@@ -605,25 +632,27 @@ __global__ __launch_bounds__(256) void k_cg_update(double *__restrict__ r, doubl
         i += kVecRows * stride;
         load(i);
     }
-    rz = block_sum_256(rz, sh);
-    rr = block_sum_256(rr, sh);
+    block_sum2_256(rz, rr, sh);
     if (threadIdx.x == 0) {
         partial[2 * blockIdx.x] = rz;
         partial[2 * blockIdx.x + 1] = rr;
     }
 }
 
-// rz_new = sum of the update's nb partial sums (kept in scal[i_new]);
+// rz_new, r.r = sums of the update's nb partial sums (kept in scal);
 // x += (rz_old / pq) p;  p = z + (rz_new / rz_old) p.
-// With test set, r.r (kept in scal[i_rr]) is compared with the tolerance and an
-// iteration that meets it records itself in *state: rr <= tol2 bb.
+// An iteration with |r| <= tol |b| records itself in *state, which ends the
+// solve: tol is rtol where the solve tests and a level below it in between (see
+// pressure_solve).  host, if given, receives {r.r, b.b, met, it} in host[0..3]
+// from a test and in host[4..7] from an iteration that ended the solve between
+// two tests.
 __global__ __launch_bounds__(256) void k_cg_direction(double *__restrict__ x, double *__restrict__ p,
                                                       const double *__restrict__ z, double *scal, int i_new, int i_old,
                                                       int i_pq, int i_rr, int i_bb, int n,
                                                       const double *__restrict__ partial, int nb, int *state, int it,
-                                                      bool test, double rtol, double *host) {
+                                                      bool test, double tol, double *host) {
     if (cg_skip(state, it)) return;
-    __shared__ double sh[4];
+    __shared__ double sh[8];
     const int64_t stride = (int64_t)gridDim.x * 256;
     int64_t i = blockIdx.x * 256 + threadIdx.x;
     double xv[kVecRows], pv[kVecRows], zv[kVecRows];
@@ -637,22 +666,20 @@ __global__ __launch_bounds__(256) void k_cg_direction(double *__restrict__ x, do
             }
     };
     load(i);
-    const double rz = partial_sum_256(partial, nb, 2, sh);
-    if (blockIdx.x == 0) {  // (its own workgroup's other work does not depend on these)
-        const double rr = test ? partial_sum_256(partial + 1, nb, 2, sh) : 0.0;
-        if (threadIdx.x == 0) {
-            scal[i_new] = rz;
-            if (test) {
-                const double bb = scal[i_bb];
-                const bool met = sqrt(rr) <= rtol * sqrt(bb);
-                scal[i_rr] = rr;
-                if (met) *state = it;
-                if (host) {
-                    host[0] = rr;
-                    host[1] = bb;
-                    host[2] = met ? 1.0 : 0.0;
-                }
-            }
+    double rz, rr;
+    partial_sum2_256(partial, nb, rz, rr, sh);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        const double bb = scal[i_bb];
+        const bool met = sqrt(rr) <= tol * sqrt(bb);
+        scal[i_new] = rz;
+        scal[i_rr] = rr;
+        if (met) *state = it;
+        if (host && (test || met)) {
+            double *rec = test ? host : host + 4;
+            rec[0] = rr;
+            rec[1] = bb;
+            rec[2] = met ? 1.0 : 0.0;
+            rec[3] = it;
         }
     }
     const double alpha = scal[i_old] / scal[i_pq];
@@ -714,7 +741,7 @@ __global__ __launch_bounds__(256) void k_sum_partial(const double *__restrict__ 
 // x -= mean(x), from the block sums of x
 __global__ __launch_bounds__(256) void k_sub_mean(double *__restrict__ x, const double *__restrict__ partial, int nb, int n) {
     __shared__ double sh[4];
-    const double m = partial_sum_256(partial, nb, 1, sh) / n;
+    const double m = partial_sum_256(partial, nb, sh) / n;
     for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) x[i] -= m;
 }
 
@@ -724,8 +751,8 @@ __global__ __launch_bounds__(256) void k_cg_setup(const double *b, const double 
                                                   double *x, double *__restrict__ r, double *__restrict__ z,
                                                   double *__restrict__ p, int n,
                                                   const double *__restrict__ partial, int nb, double *__restrict__ out) {
-    __shared__ double sh[4];
-    const double m = partial_sum_256(partial, nb, 1, sh) / n;
+    __shared__ double sh[8];
+    const double m = partial_sum_256(partial, nb, sh) / n;
     double bb = 0.0, rz = 0.0;
     for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
         const double ri = b[i] - m, zi = ri / diag[i];
@@ -736,8 +763,7 @@ __global__ __launch_bounds__(256) void k_cg_setup(const double *b, const double 
         bb += ri * ri;
         rz += ri * zi;
     }
-    bb = block_sum_256(bb, sh);
-    rz = block_sum_256(rz, sh);
+    block_sum2_256(bb, rz, sh);
     if (threadIdx.x == 0) {
         out[2 * blockIdx.x] = bb;
         out[2 * blockIdx.x + 1] = rz;
@@ -748,8 +774,9 @@ __global__ __launch_bounds__(256) void k_cg_setup(const double *b, const double 
 // with a zero right-hand side every iteration is skipped.
 __global__ __launch_bounds__(256) void k_cg_begin(const double *__restrict__ partial, int nb, double *scal, int i_bb,
                                                   int i_rz, int *state) {
-    __shared__ double sh[4];
-    const double bb = partial_sum_256(partial, nb, 2, sh), rz = partial_sum_256(partial + 1, nb, 2, sh);
+    __shared__ double sh[8];
+    double bb, rz;
+    partial_sum2_256(partial, nb, bb, rz, sh);
     if (threadIdx.x == 0) {
         scal[i_bb] = bb;
         scal[i_rz] = rz;
@@ -812,7 +839,7 @@ struct lesasm_stepper {
     int nslices = 0;
     int64_t sell_entries = 0;
     int *d_cgstate = nullptr;   // iteration that met the tolerance (see cg_skip)
-    double *h_rec = nullptr;    // pinned: the last convergence test, {r.r, b.b, met}
+    double *h_rec = nullptr;    // pinned: two records of k_cg_direction
     hipEvent_t ev_check = nullptr;  // end of the iteration that made it
 };
 
@@ -872,7 +899,7 @@ void launch_spmv(const lesasm_stepper *st, const double *p, double *q, const int
 
 // CG iteration it (1, 2, ...) for solution x.  The old and new r.z use two slots
 // alternately, so that no scalar is overwritten while a kernel may still read it.
-void launch_cg_iteration(lesasm_stepper *st, double *x, int it, bool test, double *host, hipStream_t s) {
+void launch_cg_iteration(lesasm_stepper *st, double *x, int it, bool test, double tol, double *host, hipStream_t s) {
     const int i_rz = it & 1 ? S_RZ : S_RZN, i_rzn = it & 1 ? S_RZN : S_RZ;
     int *state = st->d_cgstate;
     const dim3 g(st->vec_blocks), b(256);
@@ -881,7 +908,7 @@ void launch_cg_iteration(lesasm_stepper *st, double *x, int it, bool test, doubl
     hipLaunchKernelGGL(k_cg_update, g, b, 0, s, st->r, st->z, st->q, st->diag, st->scal, i_rz, (int)S_PQ, st->n,
                        st->partial, st->spmv_blocks, rpart, (const int *)state, it);
     hipLaunchKernelGGL(k_cg_direction, g, b, 0, s, x, st->pv, st->z, st->scal, i_rzn, i_rz, (int)S_PQ, (int)S_RR,
-                       (int)S_BB, st->n, rpart, st->vec_blocks, state, it, test, st->rtol, host);
+                       (int)S_BB, st->n, rpart, st->vec_blocks, state, it, test, tol, host);
 }
 
 // Start of a solve (before iteration 1) and its end (x to zero mean).
@@ -906,30 +933,38 @@ void launch_cg_finish(lesasm_stepper *st, double *x, hipStream_t s) {
 // kCgAhead iterations behind a test before it waits for it, so the GPU does not
 // idle while the answer travels (0.45 M rows: 36.9 against 38.8 us an iteration
 // with a copy and a wait); if the test was met they return at once.
+// Between two tests a solve also ends once the residual is a hundredth of the
+// tolerance or near rounding: K is singular on closed and periodic meshes, and
+// an iteration on a residual of rounding errors, whose constant part K cannot
+// reduce, throws the solution off (8^3 periodic cube, 17 to 32 iterations: 2 to
+// 12 % of the solves came back with residuals of 1e-8 to 1e-5).
 constexpr int kCgAhead = 4;
+constexpr double kCgRounding = 1e-14;  // of |b|
 
 int pressure_solve(lesasm_stepper *st, const double *b_in, double *x, hipStream_t s) {
+    for (int k = 0; k < 8; ++k) st->h_rec[k] = -1.0;
     launch_cg_start(st, b_in, x, s);
+    const double below = std::min(st->rtol, std::max(0.01 * st->rtol, kCgRounding));
     int queued = 0, at = 0;
     double res = 0.0;
     bool met = false;
     while (at < st->maxit && !met) {
         at = std::min(at + st->check_every, st->maxit);
         const int next = std::min(at + st->check_every, st->maxit);
-        st->h_rec[2] = -1.0;
-        while (queued < at) {
-            ++queued;
-            launch_cg_iteration(st, x, queued, queued == at, queued == at ? st->h_rec : nullptr, s);
-        }
+        auto queue = [&](int upto) {
+            while (queued < upto) {
+                ++queued;
+                launch_cg_iteration(st, x, queued, queued == at, queued == at ? st->rtol : below, st->h_rec, s);
+            }
+        };
+        queue(at);
         LESASM_HIP_TRY(hipEventRecord(st->ev_check, s));
-        while (queued < std::min(at + kCgAhead, next - 1)) {
-            ++queued;
-            launch_cg_iteration(st, x, queued, false, nullptr, s);
-        }
+        queue(std::min(at + kCgAhead, next - 1));
         LESASM_HIP_TRY(hipGetLastError());
         LESASM_HIP_TRY(hipEventSynchronize(st->ev_check));
         const volatile double *rec = st->h_rec;
-        if (rec[2] < 0.0) {  // skipped: zero right-hand side, x = 0
+        if (rec[3] != at) rec += 4;  // the test was skipped: the solve ended before it
+        if (rec[3] < 0.0) {          // or had nothing to do: zero right-hand side, x = 0
             at = 0;
             break;
         }
@@ -950,7 +985,7 @@ int pressure_solve(lesasm_stepper *st, const double *b_in, double *x, hipStream_
 int pressure_solve_captured(lesasm_stepper *st, const double *b_in, double *x, hipStream_t s, int cg_iters,
                             double *rec) {
     launch_cg_start(st, b_in, x, s);
-    for (int it = 1; it <= cg_iters; ++it) launch_cg_iteration(st, x, it, true, nullptr, s);
+    for (int it = 1; it <= cg_iters; ++it) launch_cg_iteration(st, x, it, true, st->rtol, nullptr, s);
     hipLaunchKernelGGL(k_cg_end, dim3(1), dim3(64), 0, s, (const int *)st->d_cgstate, (const double *)st->scal,
                        (int)S_RR, (int)S_BB, cg_iters, rec);
     launch_cg_finish(st, x, s);
@@ -1055,7 +1090,7 @@ extern "C" int lesasm_stepper_create(lesasm_mesh *m, double nu, double dt, doubl
         (rc = salloc(st, &st->q, (size_t)n)) || (rc = salloc(st, &st->partial, kSpmvBlocks + 2 * kVecBlocks)) ||
         (rc = salloc(st, &st->scal, S_NUM)) || (rc = salloc(st, &st->d_cgstate, 4)))
         return rc;
-    LESASM_HIP_TRY(hipHostMalloc((void **)&st->h_rec, 4 * sizeof(double), hipHostMallocCoherent));
+    LESASM_HIP_TRY(hipHostMalloc((void **)&st->h_rec, 8 * sizeof(double), hipHostMallocCoherent));
     LESASM_HIP_TRY(hipEventCreateWithFlags(&st->ev_check, hipEventDisableTiming));
     if (n) {
         LESASM_HIP_TRY(hipMemcpy(st->rowptr, rowptr.data(), sizeof(int32_t) * rowptr.size(), hipMemcpyHostToDevice));

@@ -63,3 +63,23 @@ def test_zero_right_hand_side_and_reuse(setup):
     assert torch.equal(st.pressure_solve(b), first) and st.stats() == its
     g.close()
     st.close()
+
+
+def test_periodic_solves_keep_their_accuracy(setup):
+    # few distinct eigenvalues: the residual reaches rounding between two
+    # tests, and the Laplacian cannot reduce its constant part
+    from oracle import step
+    torch, lesasm = setup[:2]
+    c = mg.periodic_tg_case(8)
+    m = lesasm.Mesh.from_arrays(c.mesh, c.vreman_c)
+    K = step.laplacian(c.mesh)
+    st = lesasm.Stepper(m, c.nu, 1e-3)
+    rng = np.random.default_rng(1)
+    for k in range(40):
+        b = np.cos(c.mesh.field_coords() @ rng.integers(-2, 3, 3)) + 1e-3 * np.sin(c.mesh.field_coords()[:, k % 3])
+        want = step.pressure_solve(K, b)
+        x = m.to_user(st.pressure_solve(m.to_internal(torch.from_numpy(b).cuda()))).cpu().numpy()
+        assert st.stats()[1] <= 1e-12, k
+        assert np.abs(x - want).max() <= 1e-9 * np.abs(want).max(), k
+    st.close()
+    m.close()
