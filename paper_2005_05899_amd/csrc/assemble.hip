@@ -9,6 +9,7 @@
 // read-modify-write with a fixed summation order.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "element.hpp"
 
@@ -67,6 +68,27 @@ __global__ __launch_bounds__(256, 2) void k_assemble_chunk_mlp(ChunkView c, cons
     extern __shared__ __align__(16) double lds[];
     chunk_body<T, R, HAS_P, PERIODIC, STAGED, true>(c, xcd_block(blockIdx.x, gridDim.x), lds, xyz, u, p, nu, cv,
                                                     rhs, &cl, lds_node_doubles);
+}
+
+// The staged scatter of a hybrid mesh with the chunks of all four types in one
+// launch, one workgroup each (see one_launch for the sizes).
+template <typename R, bool HAS_P, bool PERIODIC, bool MLP>
+__global__ __launch_bounds__(256, MLP ? 2 : 1) void k_assemble_all(ChunkViews cv, const double *__restrict__ xyz,
+                                                      const double *__restrict__ u, const double *__restrict__ p,
+                                                      double nu, double c, double *__restrict__ rhs, ClosureView cl,
+                                                      int lds_node_doubles) {
+    extern __shared__ __align__(16) double lds[];
+    const int b = blockIdx.x;
+    auto run = [&](auto type, int k) {
+        if constexpr (MLP) cl.fallbacks += kViewCat[k] * kFallbackSlots;
+        chunk_body<decltype(type)::value, R, HAS_P, PERIODIC, true, MLP>(
+            cv.v[k], xcd_block(b - cv.first[k], cv.first[k + 1] - cv.first[k]), lds, xyz, u, p, nu, c, rhs, &cl,
+            lds_node_doubles);
+    };
+    if (b < cv.first[1]) run(std::integral_constant<int, LESASM_HEX08>(), 0);
+    else if (b < cv.first[2]) run(std::integral_constant<int, LESASM_PEN06>(), 1);
+    else if (b < cv.first[3]) run(std::integral_constant<int, LESASM_PYR05>(), 2);
+    else run(std::integral_constant<int, LESASM_TET04>(), 3);
 }
 
 // Staged scatter, second phase: every node owned by no chunk sums its staging
@@ -243,6 +265,23 @@ bool mesh_is_staged(const lesasm_mesh *m) {
     return mesh_is_chunked(m) && !(m->flags & LESASM_MESH_SCATTER_CHUNK_ATOMIC);
 }
 
+ChunkViews chunk_views(const lesasm_mesh *m) {
+    ChunkViews cv{};
+    for (int k = 0; k < kNumCat; ++k) {
+        const Category &c = m->cat[kViewCat[k]];
+        cv.v[k] = ChunkView{c.d_eoff, c.d_goff, c.d_gnodes, c.d_foff, c.d_fnodes, c.d_fslot, c.d_lg, c.d_lf, c.d_delta,
+                            m->d_stage, (int32_t)c.n};
+        cv.first[k + 1] = cv.first[k] + c.n_chunks;
+    }
+    return cv;
+}
+
+bool mesh_is_periodic(const lesasm_mesh *m) {
+    for (const Category &c : m->cat)
+        if (c.d_lf != c.d_lg) return true;
+    return false;
+}
+
 // Shared nodes from which on the gather is split by class: below, one launch
 // after the join (the overlap of a few microseconds would not pay for the
 // extra launches of a small mesh).
@@ -255,6 +294,53 @@ static void launch_gather(lesasm_mesh *m, int c0, int c1, double *rhs, hipStream
     ProfileScope ps(m, LESASM_KERNEL_GATHER, s);
     hipLaunchKernelGGL(k_gather_shared, dim3((n + 255) / 256), dim3(256), 0, s, m->d_gnode + a, m->d_goffs + a,
                        m->d_stage, rhs, n);
+}
+
+// The staged scatter of a hybrid mesh in one launch on the caller's stream (and
+// one gather): forking the type kernels onto streams and joining them costs
+// 20 us of events and gaps, more than it gains until the kernels are long.  In
+// one launch every type runs with the registers and LDS of the largest, which
+// costs the types that could hold more wavefronts (TET04, all types in FP32).
+// us in one launch against four, hybrid boxes: 7 k elements 18/74, 0.25 M 36/76,
+// 1.0 M 84/106, 2.0 M 140/162, 4.0 M 283/303, 6.0 M 424/444, 9.9 M 689/696, 20 M
+// 1325/1285; FP32 7 k 17/75, 2.0 M 126/141, 3.0 M 178/180, 4.0 M 274/263; FP32
+// closure 7 k 32/78, 2.0 M 295/331, 6.0 M 872/876, 9.9 M 1418/1412; FP64 closure
+// 2.0 M 415/450, 3.0 M 634/652, 6.0 M 1275/1262.  Meshes of one type have nothing
+// to fork and keep that type's own kernel (2.0 M tetrahedra 65 against 74 us).
+constexpr int64_t kOneLaunchFp64 = 8000000, kOneLaunchOther = 3000000;
+
+static bool one_launch(const lesasm_mesh *m) {
+    int types = 0;
+    for (const Category &c : m->cat) types += c.n > 0;
+    // (profiling, other workgroup sizes and the other options keep the kernels apart)
+    if (types < 2 || !m->concurrent || m->profile || m->block != 256 || m->persist != 0) return false;
+    return m->n_elems <= (m->precision == LESASM_PREC_FP64 && !m->mlp ? kOneLaunchFp64 : kOneLaunchOther);
+}
+
+template <typename R, bool MLP>
+static void launch_all(const lesasm_mesh *m, const ClosureView &cl, const double *u, const double *p, double nu,
+                       double *rhs, hipStream_t s) {
+    const ChunkViews cv = chunk_views(m);
+    int doubles = 0;
+    for (const Category &c : m->cat) doubles = std::max(doubles, c.lds_doubles);
+    doubles = (doubles + 1) & ~1;  // the network block after the node data is 16-byte aligned
+    const size_t shm = sizeof(double) * (size_t)doubles + (MLP ? kMlpLdsBytes + 4 * kMlpWaveScratch : 0);
+    const dim3 grid(cv.first[kNumCat]), block(256);
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, block, shm, s, cv, m->d_xyz, u, p, nu, m->vreman_c, rhs, cl, doubles);
+    };
+    if (mesh_is_periodic(m)) p ? go(k_assemble_all<R, true, true, MLP>) : go(k_assemble_all<R, false, true, MLP>);
+    else p ? go(k_assemble_all<R, true, false, MLP>) : go(k_assemble_all<R, false, false, MLP>);
+}
+
+static int launch_one(lesasm_mesh *m, const ClosureView *cl, const double *u, const double *p, double nu, double *rhs,
+                      hipStream_t s) {
+    const bool f32 = m->precision == LESASM_PREC_FP32;
+    if (cl) f32 ? launch_all<float, true>(m, *cl, u, p, nu, rhs, s) : launch_all<double, true>(m, *cl, u, p, nu, rhs, s);
+    else f32 ? launch_all<float, false>(m, {}, u, p, nu, rhs, s) : launch_all<double, false>(m, {}, u, p, nu, rhs, s);
+    launch_gather(m, 0, kNumCat + 1, rhs, s);
+    LESASM_HIP_TRY(hipGetLastError());
+    return LESASM_OK;
 }
 
 // Chunked scatters: the type kernels run concurrently, the first on the
@@ -273,8 +359,10 @@ static int launch_chunked(lesasm_mesh *m, const double *u, const double *p, doub
                           m->fallback_tol * m->fallback_tol, m->d_fallbacks};
         cl = &clv;
     }
-    LESASM_HIP_TRY(hipEventRecord(m->ev_fork, s));
-    int used = 0;
+    if (staged && one_launch(m)) return launch_one(m, cl, u, p, nu, rhs, s);
+    int types = 0, used = 0;
+    for (const Category &c : m->cat) types += c.n > 0;
+    if (types > 1 && m->concurrent) LESASM_HIP_TRY(hipEventRecord(m->ev_fork, s));
     // Launch order of the categories (the first on the caller's stream, the
     // others on the side streams): HEX08, TET04, PYR05, PEN06.  Measured on the
     // hybrid mix, the order sets how the concurrent kernels share the CUs:

@@ -94,6 +94,15 @@ struct ChunkView {
     int32_t ld;     // elements in the category
 };
 
+// The chunks of every type in one launch: workgroups [first[k], first[k + 1])
+// take the chunks of v[k], in the order HEX08, PEN06, PYR05, TET04 (costliest
+// chunks first).
+struct ChunkViews {
+    ChunkView v[kNumCat];
+    int first[kNumCat + 1];
+};
+constexpr int kViewCat[kNumCat] = {3, 2, 1, 0};  // category of v[k]
+
 constexpr uint32_t kOwnedBit = 0x80000000u;
 
 const short *mlp_packed(const lesasm_mlp *p);
@@ -122,6 +131,8 @@ int grid_for(size_t n, int block);
 int assemble_into(lesasm_mesh *m, const double *u, const double *p, double nu, double dt, double *rhs, hipStream_t s,
                   bool increment);
 bool mesh_is_chunked(const lesasm_mesh *m);  // one of the chunked scatters
+ChunkViews chunk_views(const lesasm_mesh *m);
+bool mesh_is_periodic(const lesasm_mesh *m);  // field nodes apart from geometry nodes
 int launch_wall(lesasm_mesh *m, const double *u, double nu, double *rhs, hipStream_t s);
 
 // Arguments of one assembly launch over a contiguous element range of a category.

@@ -243,11 +243,6 @@ __device__ __forceinline__ void element_project(XA xa, VA va, double (&r)[GRAD ?
     }
 }
 
-struct ProjectView {
-    ChunkView v[kNumCat];      // in launch order
-    int first[kNumCat + 1];    // workgroups [first[k], first[k + 1]) take the chunks of v[k]
-};
-
 template <int T, bool GRAD, bool PERIODIC>
 __device__ __forceinline__ void project_chunk(const ChunkView &c, int j, double *lds, const double *__restrict__ xyz,
                                               const double *__restrict__ in, double *__restrict__ out) {
@@ -302,7 +297,7 @@ __device__ __forceinline__ void project_chunk(const ChunkView &c, int j, double 
 }
 
 template <bool GRAD, bool PERIODIC>
-__global__ __launch_bounds__(256) void k_project_chunks(ProjectView pv, const double *__restrict__ xyz,
+__global__ __launch_bounds__(256) void k_project_chunks(ChunkViews pv, const double *__restrict__ xyz,
                                                         const double *__restrict__ in, double *__restrict__ out) {
     extern __shared__ __align__(16) double lds[];
     const int b = blockIdx.x;
@@ -316,22 +311,13 @@ __global__ __launch_bounds__(256) void k_project_chunks(ProjectView pv, const do
 // Adds the operator's contributions into the zeroed out (chunked meshes).
 template <bool GRAD>
 void launch_project_chunks(const lesasm_mesh *m, const double *in, double *out, hipStream_t s) {
-    static constexpr int kOrder[kNumCat] = {3, 2, 1, 0};  // HEX08, PEN06, PYR05, TET04: costliest chunks first
-    ProjectView pv{};
+    const ChunkViews pv = chunk_views(m);
     int doubles = 0;
-    bool periodic = false;
-    for (int i = 0; i < kNumCat; ++i) {
-        const Category &c = m->cat[kOrder[i]];
-        pv.v[i] = ChunkView{c.d_eoff, c.d_goff, c.d_gnodes, c.d_foff, c.d_fnodes, nullptr, c.d_lg, c.d_lf, c.d_delta,
-                            nullptr, (int32_t)c.n};
-        pv.first[i + 1] = pv.first[i] + c.n_chunks;
-        doubles = std::max(doubles, c.project_doubles);
-        periodic = periodic || c.d_lf != c.d_lg;
-    }
+    for (const Category &c : m->cat) doubles = std::max(doubles, c.project_doubles);
     const dim3 grid(pv.first[kNumCat]), block(256);
     const size_t shm = sizeof(double) * (size_t)doubles;
     if (grid.x == 0) return;
-    if (periodic) hipLaunchKernelGGL((k_project_chunks<GRAD, true>), grid, block, shm, s, pv, m->d_xyz, in, out);
+    if (mesh_is_periodic(m)) hipLaunchKernelGGL((k_project_chunks<GRAD, true>), grid, block, shm, s, pv, m->d_xyz, in, out);
     else hipLaunchKernelGGL((k_project_chunks<GRAD, false>), grid, block, shm, s, pv, m->d_xyz, in, out);
 }
 
