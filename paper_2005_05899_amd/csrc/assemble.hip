@@ -307,8 +307,6 @@ static void launch_gather(lesasm_mesh *m, int c0, int c1, double *rhs, hipStream
 // closure 7 k 32/78, 2.0 M 295/331, 6.0 M 872/876, 9.9 M 1418/1412; FP64 closure
 // 2.0 M 415/450, 3.0 M 634/652, 6.0 M 1275/1262.  Meshes of one type have nothing
 // to fork and keep that type's own kernel (2.0 M tetrahedra 65 against 74 us).
-constexpr int64_t kOneLaunchFp64 = 8000000, kOneLaunchOther = 3000000;
-
 static bool one_launch(const lesasm_mesh *m) {
     int types = 0;
     for (const Category &c : m->cat) types += c.n > 0;

@@ -32,12 +32,17 @@ struct BatchEntry {
     int mesh;
 };
 
-// Per-call pointers of every mesh (written on the device by k_batch_begin).
+// Per-call pointers of every mesh: a kernel argument, or (persistent layouts)
+// written on the device by k_batch_begin.
 struct BatchCall {
     const double *u[kMaxBatch];
     const double *p[kMaxBatch];
     double *rhs[kMaxBatch];
     double nu[kMaxBatch];
+};
+
+struct BatchRhs {
+    double *v[kMaxBatch];
 };
 
 // Per-mesh arrays for the gather and update kernels.
@@ -92,10 +97,8 @@ __global__ __launch_bounds__(256) void k_batch_assemble(const BatchEntry *__rest
 
 // Per-type kernel: the same walk over the items of one element type only, so
 // each type is compiled (and occupies registers) on its own and the four run
-// concurrently.  PERSISTENT: a grid sized to fill the GPU pulls items from the
-// type's counter; otherwise one workgroup per item (item order remapped so
-// that each XCD takes a contiguous run), scheduled by the hardware.
-template <int T, typename R, bool HAS_P, bool PERSISTENT>
+// concurrently.
+template <int T, typename R, bool HAS_P>
 __global__ __launch_bounds__(256) void k_batch_assemble_type(const BatchEntry *__restrict__ entries,
                                                              const BatchCall *__restrict__ call,
                                                              const int32_t *__restrict__ wentry,
@@ -103,23 +106,55 @@ __global__ __launch_bounds__(256) void k_batch_assemble_type(const BatchEntry *_
     extern __shared__ __align__(16) double lds[];
     __shared__ int item;
     for (;;) {
-        int w;
-        if constexpr (PERSISTENT) {
-            if (threadIdx.x == 0) item = atomicAdd(head, 1);
-            __syncthreads();
-            w = item;
-            __syncthreads();
-        } else {
-            w = xcd_block(blockIdx.x, gridDim.x);
-        }
+        if (threadIdx.x == 0) item = atomicAdd(head, 1);
+        __syncthreads();
+        const int w = item;
+        __syncthreads();
         if (w >= nwork) return;
         const BatchEntry &be = entries[wentry[w]];
         const int mi = be.mesh;
         chunk_body<T, R, HAS_P, false, true>(be.v, wchunk[w], lds, be.xyz, call->u[mi], HAS_P ? call->p[mi] : nullptr,
                                              call->nu[mi], be.cv, call->rhs[mi]);
-        if constexpr (!PERSISTENT) return;
         __syncthreads();
     }
+}
+
+// One workgroup per item (item order remapped so that each XCD takes a
+// contiguous run), scheduled by the hardware: the items of one type, or
+// (k_batch_items_all) of every type in one launch, costliest type first.
+template <int T, typename R, bool HAS_P>
+__device__ __forceinline__ void batch_one_item(const BatchEntry *entries, const BatchCall &call, const int32_t *wentry,
+                                               const int32_t *wchunk, int w, double *lds) {
+    const BatchEntry &be = entries[wentry[w]];
+    const int mi = be.mesh;
+    chunk_body<T, R, HAS_P, false, true>(be.v, wchunk[w], lds, be.xyz, call.u[mi], HAS_P ? call.p[mi] : nullptr,
+                                         call.nu[mi], be.cv, call.rhs[mi]);
+}
+
+template <int T, typename R, bool HAS_P>
+__global__ __launch_bounds__(256) void k_batch_items_type(const BatchEntry *__restrict__ entries, BatchCall call,
+                                                          const int32_t *__restrict__ wentry,
+                                                          const int32_t *__restrict__ wchunk) {
+    extern __shared__ __align__(16) double lds[];
+    batch_one_item<T, R, HAS_P>(entries, call, wentry, wchunk, xcd_block(blockIdx.x, gridDim.x), lds);
+}
+
+struct BatchRanges {
+    int first[kNumCat + 1];  // workgroups [first[k], first[k + 1]) take the items of category kViewCat[k]
+    int queue[kNumCat];      // whose items start here in the (type-ordered) queue
+};
+
+template <typename R, bool HAS_P>
+__global__ __launch_bounds__(256) void k_batch_items_all(const BatchEntry *__restrict__ entries, BatchCall call,
+                                                         const int32_t *__restrict__ wentry,
+                                                         const int32_t *__restrict__ wchunk, BatchRanges rg) {
+    extern __shared__ __align__(16) double lds[];
+    const int b = blockIdx.x;
+    auto item = [&](int k) { return rg.queue[k] + xcd_block(b - rg.first[k], rg.first[k + 1] - rg.first[k]); };
+    if (b < rg.first[1]) batch_one_item<LESASM_HEX08, R, HAS_P>(entries, call, wentry, wchunk, item(0), lds);
+    else if (b < rg.first[2]) batch_one_item<LESASM_PEN06, R, HAS_P>(entries, call, wentry, wchunk, item(1), lds);
+    else if (b < rg.first[3]) batch_one_item<LESASM_PYR05, R, HAS_P>(entries, call, wentry, wchunk, item(2), lds);
+    else batch_one_item<LESASM_TET04, R, HAS_P>(entries, call, wentry, wchunk, item(3), lds);
 }
 
 // A block of at most 256 consecutive nodes of one mesh: the gather and update
@@ -134,8 +169,7 @@ constexpr int kBatchBlock = 256;
 // of shared nodes at a time (blocks over the meshes' d_gnode ranges of that
 // class), or all of them.
 __global__ __launch_bounds__(kBatchBlock) void k_batch_gather(const BatchMeshDev *__restrict__ md,
-                                                               const BatchCall *__restrict__ call,
-                                                               const BatchBlock *__restrict__ blk) {
+                                                               BatchRhs rhs, const BatchBlock *__restrict__ blk) {
     const BatchBlock bk = blk[blockIdx.x];
     const int k = bk.first + (int)threadIdx.x;
     if (k >= bk.end) return;
@@ -153,7 +187,7 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch_gather(const BatchMeshDev
         s1 += row[1];
         s2 += row[2];
     }
-    double *dst = call->rhs[bk.mesh] + 3 * (size_t)d.gnode[k];
+    double *dst = rhs.v[bk.mesh] + 3 * (size_t)d.gnode[k];
     dst[0] = s0;
     dst[1] = s1;
     dst[2] = s2;
@@ -438,10 +472,12 @@ int build_tables(lesasm_batch *b) {
 }
 
 // Gather of shared-node class c (kNumCat + 1: every class) of every mesh on s.
-void launch_batch_gather(lesasm_batch *b, int c, hipStream_t s) {
+void launch_batch_gather(lesasm_batch *b, const BatchCall &call, int c, hipStream_t s) {
     const int nb = b->blk_off[c + 1] - b->blk_off[c];
     if (nb <= 0) return;
-    hipLaunchKernelGGL(k_batch_gather, dim3((unsigned)nb), dim3(kBatchBlock), 0, s, b->d_md, b->d_call,
+    BatchRhs rhs;
+    std::copy(call.rhs, call.rhs + kMaxBatch, rhs.v);
+    hipLaunchKernelGGL(k_batch_gather, dim3((unsigned)nb), dim3(kBatchBlock), 0, s, b->d_md, rhs,
                        b->d_blk + b->blk_off[c]);
 }
 
@@ -458,45 +494,62 @@ int rebuild(lesasm_batch *b) {
     return LESASM_OK;
 }
 
-// Launch of the whole batch assembly (begin, persistent kernel, gather) on s.
+// The items of one type on s: a persistent grid that fills the GPU, or one workgroup per item.
 template <int T>
-void launch_type(lesasm_batch *b, int k, bool has_p, bool fp32, hipStream_t s) {
+void launch_type(lesasm_batch *b, const BatchCall &call, int k, bool has_p, bool fp32, hipStream_t s) {
     const int n = b->type_off[k + 1] - b->type_off[k];
     if (n <= 0) return;
-    const bool persistent = b->per_type == 1;
-    // persistent: a grid that fills the GPU; else one workgroup per item
-    const int grid = persistent ? std::max(1, std::min(n, b->n_cu * b->grid_per_cu)) : n;
     const size_t shm = sizeof(double) * (size_t)b->type_lds[k];
     const int32_t *we = b->d_wentry + b->type_off[k], *wc = b->d_wchunk + b->type_off[k];
-    int *head = b->d_head + 1 + k;
-#define LESASM_BATCH_TYPE_LAUNCH(RR, HP, PS)                                                                          \
-    hipLaunchKernelGGL((k_batch_assemble_type<T, RR, HP, PS>), dim3(grid), dim3(256), shm, s, b->d_entries, b->d_call, \
-                       we, wc, n, head)
-    if (persistent) {
-        if (fp32) {
-            if (has_p) LESASM_BATCH_TYPE_LAUNCH(float, true, true);
-            else LESASM_BATCH_TYPE_LAUNCH(float, false, true);
-        } else {
-            if (has_p) LESASM_BATCH_TYPE_LAUNCH(double, true, true);
-            else LESASM_BATCH_TYPE_LAUNCH(double, false, true);
-        }
+    if (b->per_type == 1) {
+        const dim3 grid(std::max(1, std::min(n, b->n_cu * b->grid_per_cu))), block(256);
+        int *head = b->d_head + 1 + k;
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, shm, s, b->d_entries, b->d_call, we, wc, n, head); };
+        if (fp32) has_p ? go(k_batch_assemble_type<T, float, true>) : go(k_batch_assemble_type<T, float, false>);
+        else has_p ? go(k_batch_assemble_type<T, double, true>) : go(k_batch_assemble_type<T, double, false>);
     } else {
-        if (fp32) {
-            if (has_p) LESASM_BATCH_TYPE_LAUNCH(float, true, false);
-            else LESASM_BATCH_TYPE_LAUNCH(float, false, false);
-        } else {
-            if (has_p) LESASM_BATCH_TYPE_LAUNCH(double, true, false);
-            else LESASM_BATCH_TYPE_LAUNCH(double, false, false);
-        }
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(n), dim3(256), shm, s, b->d_entries, call, we, wc); };
+        if (fp32) has_p ? go(k_batch_items_type<T, float, true>) : go(k_batch_items_type<T, float, false>);
+        else has_p ? go(k_batch_items_type<T, double, true>) : go(k_batch_items_type<T, double, false>);
     }
-#undef LESASM_BATCH_TYPE_LAUNCH
 }
 
+// One workgroup per item in one launch of every type (see one_launch in assemble.hip).
+bool batch_one_launch(const lesasm_batch *b, bool fp32) {
+    if (b->per_type != 2) return false;
+    int types = 0;
+    int64_t elems = 0;
+    for (int k = 0; k < kNumCat; ++k) types += b->type_off[k + 1] > b->type_off[k];
+    for (const lesasm_mesh *m : b->meshes) elems += m->n_elems;
+    return types > 1 && elems <= (fp32 ? kOneLaunchOther : kOneLaunchFp64);
+}
+
+void launch_items_all(lesasm_batch *b, const BatchCall &call, bool has_p, bool fp32, hipStream_t s) {
+    BatchRanges rg{};
+    int lds = 0;
+    for (int k = 0; k < kNumCat; ++k) {
+        const int c = kViewCat[k];
+        rg.first[k + 1] = rg.first[k] + b->type_off[c + 1] - b->type_off[c];
+        rg.queue[k] = b->type_off[c];
+        lds = std::max(lds, b->type_lds[c]);
+    }
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(rg.first[kNumCat]), dim3(256), sizeof(double) * (size_t)lds, s, b->d_entries,
+                           call, b->d_wentry, b->d_wchunk, rg);
+    };
+    if (fp32) has_p ? go(k_batch_items_all<float, true>) : go(k_batch_items_all<float, false>);
+    else has_p ? go(k_batch_items_all<double, true>) : go(k_batch_items_all<double, false>);
+}
+
+// Launch of the whole batch assembly on s.
 int batch_launch(lesasm_batch *b, const BatchCall &call, bool has_p, bool fp32, hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_begin, dim3(1), dim3(64), 0, s, call, b->d_call, b->d_head);
+    if (b->per_type != 2) hipLaunchKernelGGL(k_batch_begin, dim3(1), dim3(64), 0, s, call, b->d_call, b->d_head);
     const int grid = std::max(1, std::min(b->nwork, b->n_cu * b->grid_per_cu));
     const size_t shm = sizeof(double) * (size_t)b->lds_doubles;
-    if (b->per_type && b->nwork > 0) {
+    if (batch_one_launch(b, fp32)) {
+        launch_items_all(b, call, has_p, fp32, s);
+        launch_batch_gather(b, call, kNumCat + 1, s);
+    } else if (b->per_type && b->nwork > 0) {
         // the four type kernels on forked streams (order as the single-mesh
         // path: HEX08, TET04, PYR05, PEN06), joined before the gather
         LESASM_HIP_TRY(hipEventRecord(b->ev_fork, s));
@@ -512,19 +565,19 @@ int batch_launch(lesasm_batch *b, const BatchCall &call, bool has_p, bool fp32, 
             }
             ++used;
             switch (kTypes[k]) {
-            case LESASM_TET04: launch_type<LESASM_TET04>(b, k, has_p, fp32, sk); break;
-            case LESASM_PYR05: launch_type<LESASM_PYR05>(b, k, has_p, fp32, sk); break;
-            case LESASM_PEN06: launch_type<LESASM_PEN06>(b, k, has_p, fp32, sk); break;
-            case LESASM_HEX08: launch_type<LESASM_HEX08>(b, k, has_p, fp32, sk); break;
+            case LESASM_TET04: launch_type<LESASM_TET04>(b, call, k, has_p, fp32, sk); break;
+            case LESASM_PYR05: launch_type<LESASM_PYR05>(b, call, k, has_p, fp32, sk); break;
+            case LESASM_PEN06: launch_type<LESASM_PEN06>(b, call, k, has_p, fp32, sk); break;
+            case LESASM_HEX08: launch_type<LESASM_HEX08>(b, call, k, has_p, fp32, sk); break;
             }
             // the shared nodes of this type only, behind its kernel on its stream
-            launch_batch_gather(b, k, sk);
+            launch_batch_gather(b, call, k, sk);
         }
         for (int i = 0; i + 1 < used; ++i) {
             LESASM_HIP_TRY(hipEventRecord(b->ev_join[i], b->side[i]));
             LESASM_HIP_TRY(hipStreamWaitEvent(s, b->ev_join[i], 0));
         }
-        launch_batch_gather(b, kNumCat, s);  // nodes of several types, or of none
+        launch_batch_gather(b, call, kNumCat, s);  // nodes of several types, or of none
     } else if (b->nwork > 0) {
         if (fp32) {
             if (has_p) hipLaunchKernelGGL((k_batch_assemble<float, true>), dim3(grid), dim3(256), shm, s, b->d_entries, b->d_call, b->d_wentry, b->d_wchunk, b->nwork, b->d_head);
@@ -534,7 +587,7 @@ int batch_launch(lesasm_batch *b, const BatchCall &call, bool has_p, bool fp32, 
             else hipLaunchKernelGGL((k_batch_assemble<double, false>), dim3(grid), dim3(256), shm, s, b->d_entries, b->d_call, b->d_wentry, b->d_wchunk, b->nwork, b->d_head);
         }
     }
-    if (!(b->per_type && b->nwork > 0)) launch_batch_gather(b, kNumCat + 1, s);
+    if (!(b->per_type && b->nwork > 0)) launch_batch_gather(b, call, kNumCat + 1, s);
     LESASM_HIP_TRY(hipGetLastError());
     return LESASM_OK;
 }
