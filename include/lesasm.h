@@ -158,9 +158,9 @@ int lesasm_mesh_filter_width(const lesasm_mesh *mesh, double *d_out, void *strea
                                      512 elements run in blocks of 512 */
 #define LESASM_OPT_PROFILE 5      /* 1: record HIP events around every kernel launch */
 #define LESASM_OPT_CHUNK 6        /* elements per chunk of the chunked scatters, 32..4096, or 0
-                                     (default) for min(512, max(64, 2^floor(log2(n_type/256)))) per
-                                     type, 1024 for TET04 and PEN06 when that leaves at least 4096
-                                     chunks;
+                                     (default) for 512 (64 below 16384 elements in the mesh, 128 below
+                                     49152, 256 below 524288), 1024 for TET04 and PEN06 when that
+                                     leaves at least 4096 chunks of the type;
                                      setting it rebuilds the chunks (synchronises) */
 #define LESASM_OPT_CONCURRENT 7   /* 1 (default): the element-type kernels of one chunked assembly run
                                      concurrently on forked streams (joined before return); 0: one

@@ -268,14 +268,21 @@ template <class T> static void dfree(lesasm_mesh *m, T *&p) {
 // lists are sorted ascending (coalesced loads); a field node is owned by a
 // chunk when all of its incidences in the mesh lie in that chunk.
 
+// Length of a chunk of a type with n elements.  Up to some millions of elements
+// the chunks of all types run in one launch, so the length follows the whole
+// mesh: a chunk shorter than a workgroup leaves threads idle and shares more
+// nodes, while too few chunks leave compute units idle.  us per FP64 residual of
+// hybrid boxes with chunks of 64, 128, 256, 512: 7 k elements 17.1, 17.7, 18.1,
+// 25.7; 63 k 22.1, 20.5, 19.1, 27.3; 0.26 M 55.7, 40.5, 31.6, 36.6; 1.0 M 193,
+// 123, 87.9, 83.1; 2.0 M 378, 233, 155, 141 (768: 142, 1024: 142).
 static int chunk_length(const lesasm_mesh *m, int type, int64_t n) {
     if (m->chunk_elems) return m->chunk_elems;
-    int ce = 64;
-    while (ce < 512 && 2 * ce <= n / 256) ce *= 2;
+    const int64_t all = m->n_elems;
+    const int ce = all >= (1 << 19) ? 512 : all >= 49152 ? 256 : all >= 16384 ? 128 : 64;
     // TET04 and PEN06 gain from longer chunks (fewer shared nodes per element,
     // so fewer staging rows) once the category still makes at least 4096 of
     // them; HEX08 and PYR05 do not (HEX08 measured slower at 1024)
-    if ((type == LESASM_TET04 || type == LESASM_PEN06) && ce == 512 && n / 1024 >= 4096) ce = 1024;
+    if ((type == LESASM_TET04 || type == LESASM_PEN06) && n / 1024 >= 4096) return 1024;
     return ce;
 }
 
