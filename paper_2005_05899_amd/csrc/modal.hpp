@@ -19,6 +19,13 @@
 //         At a point of the collapsed rule (A, B, c): xi = A(1-c), eta = B(1-c),
 //         zeta = c, q = AB(1-c) and grad q = (B, A, AB).
 //
+// value_factored and test_factored are value and test with common factors taken
+// out (HEX08 168 of 2456 FP64 operations an element, PEN06 36 of 1458), for FP64;
+// FP32 keeps the plain order of operations, and with it its results.  20 M hybrid
+// box, with the cheaper refinement of the reciprocals: PEN06 531 against 552 us,
+// HEX08 351 against 369.  Keeping the derivatives that neighbouring points share
+// in registers (8 % fewer operations) did not shorten either kernel.
+//
 // Trial coefficients are formed in FP64 from the FP64 nodal values; the
 // coordinate field keeps only its non-constant coefficients (all differences
 // of node values), so converting them to FP32 loses nothing to cancellation.
@@ -145,6 +152,10 @@ template <> struct Modal<LESASM_HEX08> {
         return c[0] + (R)q[0] * c[1] + (R)q[1] * c[2] + (R)q[2] * c[3] + (R)q[3] * c[4] + (R)q[4] * c[5] +
                (R)q[5] * c[6] + (R)q[6] * c[7];
     }
+    // from the x-derivative d[0] of grad(): (c0 + y c_y + z c_z + yz c_yz) + x d_x
+    __host__ __device__ static double value_factored(const double *c, const double *q, const double (&d)[3]) {
+        return c[0] + q[1] * c[2] + q[2] * c[3] + q[5] * c[6] + q[0] * d[0];
+    }
     // F_m += phi_m f + grad phi_m . t  (WF false: the gradient part only)
     template <bool WF, typename R> __host__ __device__ static void test(R *F, const double *q, R f, const R (&t)[3]) {
         const R x = (R)q[0], y = (R)q[1], z = (R)q[2], xy = (R)q[3], xz = (R)q[4], yz = (R)q[5], xyz = (R)q[6];
@@ -165,6 +176,25 @@ template <> struct Modal<LESASM_HEX08> {
         F[5] += z * t[0] + x * t[2];
         F[6] += z * t[1] + y * t[2];
         F[7] += yz * t[0] + xz * t[1] + xy * t[2];
+    }
+    // with gx = x f + t_x and gy = y f + t_y
+    __host__ __device__ static void test_factored(double *F, const double *q, double f, const double (&t)[3]) {
+        const double x = q[0], y = q[1], z = q[2], xy = q[3], xz = q[4], yz = q[5];
+        const double gx = x * f + t[0], gy = y * f + t[1];
+        F[0] += f;
+        F[1] += gx;
+        F[2] += gy;
+        F[3] += z * f;
+        F[3] += t[2];
+        F[4] += y * gx;
+        F[4] += x * t[1];
+        F[5] += z * gx;
+        F[5] += x * t[2];
+        F[6] += z * gy;
+        F[6] += y * t[2];
+        F[7] += yz * gx;
+        F[7] += xz * t[1];
+        F[7] += xy * t[2];
     }
     // F_m += phi_m f
     __host__ __device__ static void test_value(double *F, const double *q, double f) {
@@ -245,6 +275,23 @@ template <> struct Modal<LESASM_PEN06> {
         F[4] += z * t[0] + r * t[2];
         F[5] += z * t[1] + s * t[2];
     }
+    __host__ __device__ static double value_factored(const double *c, const double *q, const double (&d)[3]) {
+        return value(c, q, d);
+    }
+    // with gr = r f + t_r and gs = s f + t_s
+    __host__ __device__ static void test_factored(double *F, const double *q, double f, const double (&t)[3]) {
+        const double r = q[0], s = q[1], z = q[2];
+        const double gr = r * f + t[0], gs = s * f + t[1];
+        F[0] += f;
+        F[1] += gr;
+        F[2] += gs;
+        F[3] += z * f;
+        F[3] += t[2];
+        F[4] += z * gr;
+        F[4] += r * t[2];
+        F[5] += z * gs;
+        F[5] += s * t[2];
+    }
     // F_m += phi_m f
     __host__ __device__ static void test_value(double *F, const double *q, double f) {
         F[0] += f;
@@ -296,6 +343,22 @@ template <> struct Modal<LESASM_PYR05> {
         F[2] += t[1];
         F[3] += t[2];
         F[4] += (R)q[5] * t[0] + (R)q[4] * t[1] + (R)q[6] * t[2];
+    }
+    __host__ __device__ static double value_factored(const double *c, const double *q, const double (&d)[3]) {
+        return value(c, q, d);
+    }
+    // with g = xi f + t_xi: q f + grad q . t = B g + A t_eta + AB t_zeta (q = xi B)
+    __host__ __device__ static void test_factored(double *F, const double *q, double f, const double (&t)[3]) {
+        const double g = q[0] * f + t[0];
+        F[0] += f;
+        F[1] += g;
+        F[2] += q[1] * f;
+        F[2] += t[1];
+        F[3] += q[2] * f;
+        F[3] += t[2];
+        F[4] += q[5] * g;
+        F[4] += q[4] * t[1];
+        F[4] += q[6] * t[2];
     }
     // F_m += phi_m f
     __host__ __device__ static void test_value(double *F, const double *q, double f) {
