@@ -210,7 +210,7 @@ template <typename R, bool STAGED>
 static void dispatch_chunks(const Category &c, double *stage, const ClosureView *cl, bool has_p, bool periodic,
                             int block, int persist, hipStream_t s, const double *xyz, const double *u, const double *p, double nu,
                             double cv, double *rhs) {
-    ChunkView v{c.d_eoff, c.d_goff, c.d_gnodes, c.d_foff, c.d_fnodes, c.d_fslot, c.d_lg, c.d_lf, c.d_delta, stage,
+    ChunkView v{c.d_eoff, c.d_goff, c.d_gnodes, c.d_foff, c.d_fnodes, c.d_fdst, c.d_lg, c.d_lf, c.d_delta, stage,
                 (int32_t)c.n};
     const size_t shm = sizeof(double) * (size_t)c.lds_doubles;
     // Chunks longer than 512 elements hold up to 64 KB of node data, so a
@@ -269,7 +269,7 @@ ChunkViews chunk_views(const lesasm_mesh *m) {
     ChunkViews cv{};
     for (int k = 0; k < kNumCat; ++k) {
         const Category &c = m->cat[kViewCat[k]];
-        cv.v[k] = ChunkView{c.d_eoff, c.d_goff, c.d_gnodes, c.d_foff, c.d_fnodes, c.d_fslot, c.d_lg, c.d_lf, c.d_delta,
+        cv.v[k] = ChunkView{c.d_eoff, c.d_goff, c.d_gnodes, c.d_foff, c.d_fnodes, c.d_fdst, c.d_lg, c.d_lf, c.d_delta,
                             m->d_stage, (int32_t)c.n};
         cv.first[k + 1] = cv.first[k] + c.n_chunks;
     }

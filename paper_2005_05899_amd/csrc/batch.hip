@@ -372,7 +372,7 @@ int build_work(lesasm_batch *b) {
             const int ng = c.type == LESASM_TET04 ? 4 : (c.type == LESASM_PEN06 ? 6 : 8);
             const int eid = (int)entries.size();
             BatchEntry be;
-            be.v = ChunkView{c.d_eoff, c.d_goff, c.d_gnodes, c.d_foff, c.d_fnodes, c.d_fslot, c.d_lg, c.d_lf,
+            be.v = ChunkView{c.d_eoff, c.d_goff, c.d_gnodes, c.d_foff, c.d_fnodes, c.d_fdst, c.d_lg, c.d_lf,
                              c.d_delta, m->d_stage, (int32_t)c.n};
             be.xyz = m->d_xyz;
             be.cv = m->vreman_c;

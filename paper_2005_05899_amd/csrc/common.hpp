@@ -77,7 +77,7 @@ struct Category {
     int32_t *d_fnodes = nullptr;   // field nodes of each chunk; bit 31 set if the chunk owns the node
     uint16_t *d_lg = nullptr;      // [nnode][n] chunk-local geometry index of each element slot
     uint16_t *d_lf = nullptr;      // [nnode][n] chunk-local field index (aliases d_lg without a field map)
-    int32_t *d_fslot = nullptr;    // per d_fnodes entry: staging slot of a shared node, -1 if owned
+    int32_t *d_fdst = nullptr;     // per d_fnodes entry: the node, with bit 31 set, if owned, else its staging row
     int lds_doubles = 0;           // largest LDS footprint of a chunk, in doubles
     int project_doubles = 0;       // the same for the divergence and gradient kernels
     int chunk_elems = 0;           // chunk length used for this category
@@ -87,7 +87,7 @@ struct Category {
 
 // Arguments of one chunked launch (one workgroup per chunk).
 struct ChunkView {
-    const int32_t *eoff, *goff, *gnodes, *foff, *fnodes, *fslot;
+    const int32_t *eoff, *goff, *gnodes, *foff, *fnodes, *fdst;
     const uint16_t *lg, *lf;
     const double *delta;
     double *stage;  // staging rows [slot][3] for shared nodes

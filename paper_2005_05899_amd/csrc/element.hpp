@@ -461,6 +461,19 @@ struct ClosureView {
     unsigned long long *fallbacks;
 };
 
+// Nodes of a thread on their way at a time while a chunk is staged and written
+// back.  A chunk begins and ends with chains of dependent loads (ids, then
+// values; target rows, then stores) during which its workgroup issues nothing,
+// and one or two others share its CU.  With ids, coordinates, velocities and
+// pressures of kStage nodes under way together, one index per node for the
+// write-back (d_fdst; before, the tag and then the staging slot) and that index
+// loaded before the last barrier, measured in us (one node and one list at a
+// time before): 20 M FP64 1240 -> 1155 (HEX08 352 -> 311, PEN06 534 -> 484,
+// TET04 165 -> 152, PYR05 84 -> 80), 20 M FP32 1037 -> 933, 2.0 M FP64
+// 138.7 -> 132, 2.0 M FP32 126.7 -> 113.8.  One node at a time with the lists
+// fused: 1189 / 949; three: 1153 / 941 (PYR05 FP32 66 instead of 61).
+constexpr int kStage = 2;
+
 template <int T, typename R, bool HAS_P, bool PERIODIC, bool STAGED, bool MLP = false>
 __device__ __forceinline__ void chunk_body(const ChunkView &c, int j, double *lds, const double *__restrict__ xyz,
                                            const double *__restrict__ u, const double *__restrict__ p, double nu,
@@ -473,20 +486,49 @@ __device__ __forceinline__ void chunk_body(const ChunkView &c, int j, double *ld
     const int nf = PERIODIC ? c.foff[j + 1] - f0 : ng;
     double *sx = lds, *su = sx + 3 * ng, *sp = su + 3 * nf, *sacc = sp + nf;
 
-    for (int k = threadIdx.x; k < ng; k += blockDim.x) {
-        const size_t g = (size_t)c.gnodes[g0 + k];
-        sx[3 * k + 0] = xyz[3 * g + 0];
-        sx[3 * k + 1] = xyz[3 * g + 1];
-        sx[3 * k + 2] = xyz[3 * g + 2];
+    const int step = (int)blockDim.x;
+    for (int k0 = threadIdx.x; k0 < ng; k0 += kStage * step) {
+        uint32_t id[kStage];
+        double v[kStage][PERIODIC ? 3 : 7];
+#pragma unroll
+        for (int j = 0; j < kStage; ++j)
+            if (k0 + j * step < ng) id[j] = (uint32_t)c.gnodes[g0 + k0 + j * step];
+#pragma unroll
+        for (int j = 0; j < kStage; ++j)
+            if (k0 + j * step < ng) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) v[j][i] = xyz[3 * (size_t)id[j] + i];
+                if constexpr (!PERIODIC) {  // the field nodes are the geometry nodes
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) v[j][3 + i] = u[3 * (size_t)id[j] + i];
+                    v[j][6] = HAS_P ? p[id[j]] : 0.0;
+                }
+            }
+#pragma unroll
+        for (int j = 0; j < kStage; ++j) {
+            const int k = k0 + j * step;
+            if (k < ng) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    sx[3 * k + i] = v[j][i];
+                    if constexpr (!PERIODIC) {
+                        su[3 * k + i] = v[j][3 + i];
+                        sacc[3 * k + i] = 0.0;
+                    }
+                }
+                if constexpr (!PERIODIC) sp[k] = v[j][6];
+            }
+        }
     }
-    for (int k = threadIdx.x; k < nf; k += blockDim.x) {
-        const size_t f = (size_t)((uint32_t)c.fnodes[f0 + k] & ~kOwnedBit);
-        su[3 * k + 0] = u[3 * f + 0];
-        su[3 * k + 1] = u[3 * f + 1];
-        su[3 * k + 2] = u[3 * f + 2];
-        sp[k] = HAS_P ? p[f] : 0.0;
-        sacc[3 * k + 0] = sacc[3 * k + 1] = sacc[3 * k + 2] = 0.0;
-    }
+    if constexpr (PERIODIC)
+        for (int k = threadIdx.x; k < nf; k += blockDim.x) {
+            const size_t f = (size_t)((uint32_t)c.fnodes[f0 + k] & ~kOwnedBit);
+            su[3 * k + 0] = u[3 * f + 0];
+            su[3 * k + 1] = u[3 * f + 1];
+            su[3 * k + 2] = u[3 * f + 2];
+            sp[k] = HAS_P ? p[f] : 0.0;
+            sacc[3 * k + 0] = sacc[3 * k + 1] = sacc[3 * k + 2] = 0.0;
+        }
     if constexpr (MLP) mlp_stage(cl->packed, cl->bias, (unsigned char *)(lds + lds_node_doubles));
     __syncthreads();
 
@@ -567,24 +609,43 @@ __device__ __forceinline__ void chunk_body(const ChunkView &c, int j, double *ld
         }
         if (fallbacks) atomicAdd(cl->fallbacks + (blockIdx.x & (kFallbackSlots - 1)), (unsigned long long)fallbacks);
     }
-    __syncthreads();
-
-    for (int k = threadIdx.x; k < nf; k += blockDim.x) {
-        const uint32_t tag = (uint32_t)c.fnodes[f0 + k];
-        double *dst = rhs + 3 * (size_t)(tag & ~kOwnedBit);
-        if (tag & kOwnedBit) {
-            dst[0] = sacc[3 * k + 0];
-            dst[1] = sacc[3 * k + 1];
-            dst[2] = sacc[3 * k + 2];
-        } else if (STAGED) {
-            double *row = c.stage + 3 * (size_t)c.fslot[f0 + k];
-            row[0] = sacc[3 * k + 0];
-            row[1] = sacc[3 * k + 1];
-            row[2] = sacc[3 * k + 2];
-        } else {
-            unsafeAtomicAdd(dst + 0, sacc[3 * k + 0]);
-            unsafeAtomicAdd(dst + 1, sacc[3 * k + 1]);
-            unsafeAtomicAdd(dst + 2, sacc[3 * k + 2]);
+    if constexpr (STAGED) {
+        // owned: the node's row of rhs, shared: its staging row (one index for both);
+        // a thread's first indices are on their way while it waits for the others
+        uint32_t to[kStage];
+#pragma unroll
+        for (int i = 0; i < kStage; ++i)
+            if ((int)threadIdx.x + i * step < nf) to[i] = (uint32_t)c.fdst[f0 + threadIdx.x + i * step];
+        __syncthreads();
+        for (int k0 = threadIdx.x; k0 < nf; k0 += kStage * step) {
+            if (k0 >= kStage * step)
+#pragma unroll
+                for (int i = 0; i < kStage; ++i)
+                    if (k0 + i * step < nf) to[i] = (uint32_t)c.fdst[f0 + k0 + i * step];
+#pragma unroll
+            for (int i = 0; i < kStage; ++i) {
+                const int k = k0 + i * step;
+                if (k >= nf) continue;
+                double *row = (to[i] & kOwnedBit ? rhs : c.stage) + 3 * (size_t)(to[i] & ~kOwnedBit);
+                row[0] = sacc[3 * k + 0];
+                row[1] = sacc[3 * k + 1];
+                row[2] = sacc[3 * k + 2];
+            }
+        }
+    } else {
+        __syncthreads();
+        for (int k = threadIdx.x; k < nf; k += blockDim.x) {
+            const uint32_t tag = (uint32_t)c.fnodes[f0 + k];
+            double *dst = rhs + 3 * (size_t)(tag & ~kOwnedBit);
+            if (tag & kOwnedBit) {
+                dst[0] = sacc[3 * k + 0];
+                dst[1] = sacc[3 * k + 1];
+                dst[2] = sacc[3 * k + 2];
+            } else {
+                unsafeAtomicAdd(dst + 0, sacc[3 * k + 0]);
+                unsafeAtomicAdd(dst + 1, sacc[3 * k + 1]);
+                unsafeAtomicAdd(dst + 2, sacc[3 * k + 2]);
+            }
         }
     }
 }

@@ -288,7 +288,7 @@ static int chunk_length(const lesasm_mesh *m, int type, int64_t n) {
 
 static int build_chunks(lesasm_mesh *m, int k) {
     Category &c = m->cat[k];
-    dfree(m, c.d_fslot);
+    dfree(m, c.d_fdst);
     c.h_fnodes.clear();
     dfree(m, c.d_eoff);
     dfree(m, c.d_goff);
@@ -428,14 +428,14 @@ static int build_staging(lesasm_mesh *m) {
             }
         m->gather_off[g + 1] = (int32_t)gnode.size();
     }
-    std::vector<std::vector<int32_t>> fslot(kNumCat);
+    std::vector<std::vector<int32_t>> fdst(kNumCat);
     for (int k = 0; k < kNumCat; ++k) {
         Category &c = m->cat[k];
-        dfree(m, c.d_fslot);
-        fslot[k].assign(c.h_fnodes.size(), -1);
+        dfree(m, c.d_fdst);
+        fdst[k] = c.h_fnodes;
         for (size_t q = 0; q < c.h_fnodes.size(); ++q) {
             const uint32_t tag = (uint32_t)c.h_fnodes[q];
-            if (!(tag & kOwnedBit)) fslot[k][q] = pos[(int32_t)(tag & ~kOwnedBit)]++;
+            if (!(tag & kOwnedBit)) fdst[k][q] = pos[(int32_t)(tag & ~kOwnedBit)]++;
         }
     }
     m->n_slots = total;
@@ -445,7 +445,7 @@ static int build_staging(lesasm_mesh *m) {
     if ((st = upload(m, &m->d_gnode, gnode))) return st;
     if ((st = upload(m, &m->d_goffs, goffs))) return st;
     for (int k = 0; k < kNumCat; ++k)
-        if ((st = upload(m, &m->cat[k].d_fslot, fslot[k]))) return st;
+        if ((st = upload(m, &m->cat[k].d_fdst, fdst[k]))) return st;
     return LESASM_OK;
 }
 
