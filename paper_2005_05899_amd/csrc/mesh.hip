@@ -354,7 +354,7 @@ static int build_chunks(lesasm_mesh *m, int k) {
             fslot[f] = -1;
         }
         c.lds_doubles = std::max(c.lds_doubles, (int)(3 * gl.size() + 7 * fl.size()));
-        c.project_doubles = std::max(c.project_doubles, (int)(3 * gl.size() + 4 * fl.size()));
+        c.project_doubles = std::max(c.project_doubles, (int)(3 * gl.size() + 4 * fl.size() + (fl.size() + 1) / 2));
         // chunk node lists are indexed with int32 offsets on the GPU
         if (gnodes.size() >= (size_t)INT32_MAX || fnodes.size() >= (size_t)INT32_MAX)
             return fail(LESASM_E_UNSUPPORTED, "mesh_create: chunk node lists of one element type exceed 2^31 entries");

@@ -158,9 +158,11 @@ __global__ __launch_bounds__(256) void k_gradient(CatView c, const double *__res
 //   (D u)_a = sum_g w N_a tr(Gx adj),   (G p)_a = sum_g w N_a px adj
 // need no division; nodes enter (relative to the element's node 0, as above)
 // and leave through the modal coefficients.
-// 2.0 M hybrid box: gradient 87 us against 1200 (four kernels), divergence 66
+// 2.0 M hybrid box: gradient 79 us against 1200 (four kernels), divergence 60
 // against 307.  One thread per output entry in the write-back, not per node, so
-// that a wavefront's atomics fill cache lines: gradient 87 against 139 us.
+// that a wavefront's atomics fill cache lines: gradient 87 against 139 us; then
+// 79 (divergence 66 -> 60) with the nodes of a chunk loaded as in chunk_body and
+// their tags kept in LDS.
 template <int T, bool GRAD, class XA, class VA>
 __device__ __forceinline__ void element_project(XA xa, VA va, double (&r)[GRAD ? 3 : 1][Ref<T>::nn]) {
     constexpr int nn = Ref<T>::nn, NI = GRAD ? 1 : 3, NO = GRAD ? 3 : 1;
@@ -252,17 +254,46 @@ __device__ __forceinline__ void project_chunk(const ChunkView &c, int j, double 
     const int f0 = PERIODIC ? c.foff[j] : g0;
     const int nf = PERIODIC ? c.foff[j + 1] - f0 : ng;
     double *sx = lds, *sv = sx + 3 * ng, *sacc = sv + NI * nf;
-    for (int k = threadIdx.x; k < ng; k += blockDim.x) {
-        const size_t g = (size_t)c.gnodes[g0 + k];
+    uint32_t *stag = (uint32_t *)(sacc + NO * nf);  // the write-back waits for no index
+    const int step = (int)blockDim.x;
+    if constexpr (PERIODIC)
+        for (int k = threadIdx.x; k < ng; k += step) {
+            const size_t g = (size_t)c.gnodes[g0 + k];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) sx[3 * k + i] = xyz[3 * g + i];
-    }
-    for (int k = threadIdx.x; k < nf; k += blockDim.x) {
-        const size_t f = (size_t)((uint32_t)c.fnodes[f0 + k] & ~kOwnedBit);
+            for (int i = 0; i < 3; ++i) sx[3 * k + i] = xyz[3 * g + i];
+        }
+    // kStage nodes of a thread under way together, as in chunk_body
+    for (int k0 = threadIdx.x; k0 < nf; k0 += kStage * step) {
+        uint32_t tag[kStage];
+        double x[kStage][3], v[kStage][NI];
 #pragma unroll
-        for (int i = 0; i < NI; ++i) sv[NI * k + i] = in[NI * f + i];
+        for (int q = 0; q < kStage; ++q)
+            if (k0 + q * step < nf) tag[q] = (uint32_t)c.fnodes[f0 + k0 + q * step];
 #pragma unroll
-        for (int o = 0; o < NO; ++o) sacc[NO * k + o] = 0.0;
+        for (int q = 0; q < kStage; ++q)
+            if (k0 + q * step < nf) {
+                const size_t f = tag[q] & ~kOwnedBit;
+                if constexpr (!PERIODIC) {  // the field nodes are the geometry nodes
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) x[q][i] = xyz[3 * f + i];
+                }
+#pragma unroll
+                for (int i = 0; i < NI; ++i) v[q][i] = in[NI * f + i];
+            }
+#pragma unroll
+        for (int q = 0; q < kStage; ++q) {
+            const int k = k0 + q * step;
+            if (k >= nf) continue;
+            stag[k] = tag[q];
+            if constexpr (!PERIODIC) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) sx[3 * k + i] = x[q][i];
+            }
+#pragma unroll
+            for (int i = 0; i < NI; ++i) sv[NI * k + i] = v[q][i];
+#pragma unroll
+            for (int o = 0; o < NO; ++o) sacc[NO * k + o] = 0.0;
+        }
     }
     __syncthreads();
     for (int base = e0; base < e1; base += blockDim.x) {
@@ -289,7 +320,7 @@ __device__ __forceinline__ void project_chunk(const ChunkView &c, int j, double 
     // one thread per entry, so that the atomics of neighbouring lanes fall into the same cache lines
     for (int t = threadIdx.x; t < NO * nf; t += blockDim.x) {
         const int k = t / NO;
-        const uint32_t tag = (uint32_t)c.fnodes[f0 + k];
+        const uint32_t tag = stag[k];
         double *dst = out + NO * (size_t)(tag & ~kOwnedBit) + (t - NO * k);
         if (tag & kOwnedBit) *dst = sacc[t];
         else unsafeAtomicAdd(dst, sacc[t]);
