@@ -301,18 +301,19 @@ static void launch_gather(lesasm_mesh *m, int c0, int c1, double *rhs, hipStream
 // 20 us of events and gaps, more than it gains until the kernels are long.  In
 // one launch every type runs with the registers and LDS of the largest, which
 // costs the types that could hold more wavefronts (TET04, all types in FP32).
-// us in one launch against four, hybrid boxes: 7 k elements 18/74, 0.25 M 36/76,
-// 1.0 M 84/106, 2.0 M 140/162, 4.0 M 283/303, 6.0 M 424/444, 9.9 M 689/696, 20 M
-// 1325/1285; FP32 7 k 17/75, 2.0 M 126/141, 3.0 M 178/180, 4.0 M 274/263; FP32
-// closure 7 k 32/78, 2.0 M 295/331, 6.0 M 872/876, 9.9 M 1418/1412; FP64 closure
-// 2.0 M 415/450, 3.0 M 634/652, 6.0 M 1275/1262.  Meshes of one type have nothing
+// us in one launch against four, hybrid boxes: FP64 7 k elements 17/86, 0.26 M
+// 30/84, 1.0 M 78/95, 2.0 M 134/157, 4.0 M 251/270, 6.0 M 365/380, 9.9 M 591/598,
+// 20 M 1128/1130; FP32 1.0 M 67/84, 2.0 M 114/132, 3.0 M 166/169, 4.0 M 240/237,
+// 6.0 M 361/343; closure in FP32 2.0 M 275/313, 4.0 M 533/555, 6.0 M 808/822,
+// 9.9 M 1316/1318, in FP64 1.0 M 230/236, 2.0 M 401/422, 3.0 M 610/600, 6.0 M
+// 1228/1156.  Meshes of one type have nothing
 // to fork and keep that type's own kernel (2.0 M tetrahedra 65 against 74 us).
 static bool one_launch(const lesasm_mesh *m) {
     int types = 0;
     for (const Category &c : m->cat) types += c.n > 0;
     // (profiling, other workgroup sizes and the other options keep the kernels apart)
     if (types < 2 || !m->concurrent || m->profile || m->block != 256 || m->persist != 0) return false;
-    return m->n_elems <= (m->precision == LESASM_PREC_FP64 && !m->mlp ? kOneLaunchFp64 : kOneLaunchOther);
+    return m->n_elems <= ((m->precision == LESASM_PREC_FP64) != (m->mlp != nullptr) ? kOneLaunchLong : kOneLaunchShort);
 }
 
 template <typename R, bool MLP>
