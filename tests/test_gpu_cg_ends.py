@@ -23,7 +23,7 @@ def setup():
 
 
 @pytest.mark.parametrize("rtol, maxit", [(0.5, 100), (1e-3, 100), (1e-6, 100), (1e-6, 17), (1e-300, 1), (1e-300, 15),
-                                         (1e-300, 16), (1e-300, 18), (1e-300, 33), (1e-10, 5000)])
+                                         (1e-300, 16), (1e-300, 18), (1e-300, 33)])
 def test_stops_after_the_tested_iteration(setup, rtol, maxit):
     from oracle import cg
     torch, lesasm, c, m, K = setup
