@@ -58,9 +58,11 @@ __global__ __launch_bounds__(sizeof(R) == 4 ? 512 : 256) void k_assemble_chunk(C
 }
 
 // The same with the learned closure (network weights after the node data in
-// LDS), with a register budget of two wavefronts per SIMD (see mlp_passes).
+// LDS), with a register budget of two wavefronts per SIMD (see mlp_passes); of
+// three for the FP32 PYR05 kernel, which is two registers above it by itself
+// (20 M hybrid box: 209 against 245 us).
 template <int T, typename R, bool HAS_P, bool PERIODIC, bool STAGED>
-__global__ __launch_bounds__(256, 2) void k_assemble_chunk_mlp(ChunkView c, const double *__restrict__ xyz,
+__global__ __launch_bounds__(256, T == LESASM_PYR05 && sizeof(R) == 4 ? 3 : 2) void k_assemble_chunk_mlp(ChunkView c, const double *__restrict__ xyz,
                                                             const double *__restrict__ u,
                                                             const double *__restrict__ p, double nu, double cv,
                                                             double *__restrict__ rhs, ClosureView cl,
