@@ -218,8 +218,8 @@ static void dispatch_chunks(const Category &c, double *stage, const ClosureView 
     // Chunks longer than 512 elements hold up to 64 KB of node data, so a
     // compute unit keeps two of them: workgroups of 256 threads then cap the
     // FP32 kernels below the wavefronts their registers allow.  Those run in
-    // workgroups of 512 threads (20 M hybrid box, FP32: PEN06 373 against 554
-    // us, TET04 146 against 164).  Measured and not taken: 384 threads for the
+    // workgroups of 512 threads (20 M hybrid box, FP32, when measured: PEN06 373
+    // against 554 us, TET04 146 against 164; they take 353 and 142 now).  Measured and not taken: 384 threads for the
     // FP32 HEX08 kernel (chunks of 512, three wavefronts per SIMD by its
     // registers), 551 against 352 us; 512 threads for the FP64 TET04 kernel,
     // 192 against 184 us.

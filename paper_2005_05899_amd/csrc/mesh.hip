@@ -272,9 +272,10 @@ template <class T> static void dfree(lesasm_mesh *m, T *&p) {
 // the chunks of all types run in one launch, so the length follows the whole
 // mesh: a chunk shorter than a workgroup leaves threads idle and shares more
 // nodes, while too few chunks leave compute units idle.  us per FP64 residual of
-// hybrid boxes with chunks of 64, 128, 256, 512: 7 k elements 17.1, 17.7, 18.1,
-// 25.7; 63 k 22.1, 20.5, 19.1, 27.3; 0.26 M 55.7, 40.5, 31.6, 36.6; 1.0 M 193,
-// 123, 87.9, 83.1; 2.0 M 378, 233, 155, 141 (768: 142, 1024: 142).
+// hybrid boxes with chunks of 64, 128, 256, 512: 20.8 k elements 16.6, 17.1; 63 k
+// 21.1, 20.1, 18.2, 25.3; 0.26 M 49.7, 38.2, 29.3, 34.1; 0.49 M 87.0, 62.9, 47.0,
+// 44.6; 1.0 M 163, 112, 82.2, 77.9; 2.0 M -, 212, 147, 136 (768: 136).  (FP32, chosen
+// later than the chunks, has its best at 256 up to 4 M: 2.0 M 149, 105, 114.)
 static int chunk_length(const lesasm_mesh *m, int type, int64_t n) {
     if (m->chunk_elems) return m->chunk_elems;
     const int64_t all = m->n_elems;
