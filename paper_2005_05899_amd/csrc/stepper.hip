@@ -516,16 +516,19 @@ constexpr int kSlice = 64;  // rows per slice of the sliced-ELLPACK copy (one wa
 
 // Entries j .. j + U - 1 of a slice's 64 rows: columns and values.  The loads go
 // through a buffer descriptor of the slice's extent, so entries past its width
-// cost no branch and no traffic (they read as 0 and are not added).
+// cost no branch and no traffic (they read as 0 and are not added).  The whole
+// position is in the lane offset, which the descriptor's extent bounds; the scalar
+// offset operand is 0, because the bounds check does not cover it.
 template <bool NT, int U> struct SellBatch {
     int c[U];
     double v[U];
     __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t cols, __amdgpu_buffer_rsrc_t vals, unsigned lane, int j) {
         constexpr int aux = NT ? 2 : 0;  // nontemporal
+        const unsigned at = lane + kSlice * (unsigned)j;
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            c[k] = (int)__builtin_amdgcn_raw_buffer_load_b32(cols, 4 * lane, 4 * kSlice * (j + k), aux);
-            v[k] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(vals, 8 * lane, 8 * kSlice * (j + k), aux));
+            c[k] = (int)__builtin_amdgcn_raw_buffer_load_b32(cols, 4 * at + 4 * kSlice * k, 0, aux);
+            v[k] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(vals, 8 * at + 8 * kSlice * k, 0, aux));
         }
     }
     __device__ __forceinline__ void gather(const double *__restrict__ p, double (&g)[U]) const {
