@@ -270,7 +270,8 @@ int lesasm_stepper_stats(const lesasm_stepper *stepper, int *cg_iters, double *c
  * every iteration and the iterations after the one that met the stepper's
  * rtol return at once (a replay that needs more than cg_iters ends the step
  * with the unconverged solve: lesasm_step_graph_stats tells).  The eager step
- * tests every 16 iterations, so it may run up to 15 more.
+ * tests every 16 iterations, so it may run up to 15 more (it ends between two
+ * tests only with a residual at rounding, 1e-14 of the right-hand side).
  * Bound at creation to d_u [n_field_nodes][3] and d_p [n_field_nodes]
  * (internal order, caller-owned, updated in place by every replay) and to the
  * stepper's work arrays: the stepper and mesh must outlive the graph, and

@@ -953,18 +953,19 @@ void launch_cg_finish(lesasm_stepper *st, double *x, hipStream_t s) {
 // kCgAhead iterations behind a test before it waits for it, so the GPU does not
 // idle while the answer travels (0.45 M rows: 36.9 against 38.8 us an iteration
 // with a copy and a wait); if the test was met they return at once.
-// Between two tests a solve also ends once the residual is a hundredth of the
-// tolerance or near rounding: K is singular on closed and periodic meshes, and
-// an iteration on a residual of rounding errors, whose constant part K cannot
-// reduce, throws the solution off (8^3 periodic cube, 17 to 32 iterations: 2 to
-// 12 % of the solves came back with residuals of 1e-8 to 1e-5).
+// Between two tests a solve also ends once the residual is at rounding: K is
+// singular on closed and periodic meshes, and an iteration on a residual of
+// rounding errors, whose constant part K cannot reduce, throws the solution off
+// (8^3 periodic cube, 17 to 32 iterations: 2 to 12 % of the solves came back with
+// residuals of 1e-8 to 1e-5).  Above rounding it goes on to the test whatever the
+// tolerance: on a coarse one the iterations up to it are worth digits.
 constexpr int kCgAhead = 4;
 constexpr double kCgRounding = 1e-14;  // of |b|
 
 int pressure_solve(lesasm_stepper *st, const double *b_in, double *x, hipStream_t s) {
     for (int k = 0; k < 8; ++k) st->h_rec[k] = -1.0;
     launch_cg_start(st, b_in, x, s);
-    const double below = std::min(st->rtol, std::max(0.01 * st->rtol, kCgRounding));
+    const double below = std::min(st->rtol, kCgRounding);
     int queued = 0, at = 0;
     double res = 0.0;
     bool met = false;
