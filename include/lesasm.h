@@ -257,7 +257,8 @@ int lesasm_stepper_rk3_stages(lesasm_stepper *stepper, const double *d_u, const 
 /* Mean-zero solution of K x = b - mean(b) by Jacobi-PCG.  Synchronises. */
 int lesasm_pressure_solve(lesasm_stepper *stepper, const double *d_b, double *d_x, void *stream);
 
-/* CG iterations and relative residual of the last pressure solve. */
+/* CG iterations run by the last pressure solve and the relative residual after
+ * them. */
 int lesasm_stepper_stats(const lesasm_stepper *stepper, int *cg_iters, double *cg_rel_residual);
 
 /* ---- step graph: one whole time step as a HIP graph ---------------------- */

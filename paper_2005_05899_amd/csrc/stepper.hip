@@ -966,7 +966,7 @@ int pressure_solve(lesasm_stepper *st, const double *b_in, double *x, hipStream_
     for (int k = 0; k < 8; ++k) st->h_rec[k] = -1.0;
     launch_cg_start(st, b_in, x, s);
     const double below = std::min(st->rtol, kCgRounding);
-    int queued = 0, at = 0;
+    int queued = 0, at = 0, iters = 0;
     double res = 0.0;
     bool met = false;
     while (at < st->maxit && !met) {
@@ -985,14 +985,12 @@ int pressure_solve(lesasm_stepper *st, const double *b_in, double *x, hipStream_
         LESASM_HIP_TRY(hipEventSynchronize(st->ev_check));
         const volatile double *rec = st->h_rec;
         if (rec[3] != at) rec += 4;  // the test was skipped: the solve ended before it
-        if (rec[3] < 0.0) {          // or had nothing to do: zero right-hand side, x = 0
-            at = 0;
-            break;
-        }
+        if (rec[3] < 0.0) break;     // or had nothing to do: zero right-hand side, x = 0
+        iters = (int)rec[3];
         res = std::sqrt(rec[0]) / std::sqrt(rec[1]);
         met = rec[2] > 0.0;
     }
-    st->last_iters = at;
+    st->last_iters = iters;
     st->last_res = res;
     launch_cg_finish(st, x, s);
     LESASM_HIP_TRY(hipGetLastError());

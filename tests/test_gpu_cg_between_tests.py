@@ -1,6 +1,6 @@
 """A solve between two of its convergence tests (every 16 iterations): it goes on
 to the next test while the residual is above rounding, however coarse the
-tolerance."""
+tolerance, and reports the iterations that it ran."""
 import numpy as np
 import pytest
 
@@ -37,3 +37,25 @@ def test_coarse_tolerance_runs_to_its_test(cube, rtol):
     want = cg.jacobi_pcg(K, b, 16, rtol=0.0)[0]
     assert it == 16 and res <= 1e-10
     assert np.abs(got - want).max() <= 1e-9 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("modes", [1, 2, 3, 4])
+def test_reported_iterations_are_those_run(cube, modes):
+    # as many distinct eigenvalues as modes: CG ends after that many iterations
+    # (the oracle's residual is then below 6e-15, and below 5e-16 one iteration
+    # on), long before its first test
+    torch, lesasm, c, m, K, x = cube
+    parts = [np.cos(x[:, 0]), np.cos(2 * x[:, 1]), np.cos(x[:, 0] + x[:, 1]), np.cos(3 * x[:, 2])]
+    b = m.to_internal(torch.from_numpy(sum(parts[:modes])).cuda())
+    st = lesasm.Stepper(m, c.nu, 1e-3)
+    for _ in range(2):
+        st.pressure_solve(b)
+        it, res = st.stats()
+        assert modes <= it <= modes + 1 and res <= 1e-14
+    st.close()
+    # and after one iteration less a solve reports a residual above rounding
+    if modes > 1:
+        st = lesasm.Stepper(m, c.nu, 1e-3, maxit=modes - 1)
+        st.pressure_solve(b)
+        assert st.stats()[0] == modes - 1 and st.stats()[1] > 1e-2
+        st.close()
