@@ -57,12 +57,12 @@ __device__ __forceinline__ f32x4_t relu4(f32x4_t v) {
 }
 
 // Inputs of sample s (lane j + 16 q: features 4 t + q), the constant 1 as
-// feature 10; a sample past the end has zero inputs.
+// feature 10; a sample past the end has zeros, the constant included.
 __device__ __forceinline__ void net_inputs(const float *__restrict__ X, int64_t s, int n, int q, float (&x)[3]) {
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
         const int f = 4 * t + q;
-        x[t] = f == kMlpIn ? 1.f : (f < kMlpIn && s < n) ? X[s * kMlpIn + f] : 0.f;
+        x[t] = s >= n || f > kMlpIn ? 0.f : f == kMlpIn ? 1.f : X[s * kMlpIn + f];
     }
 }
 
@@ -146,6 +146,10 @@ __global__ __launch_bounds__(256) void k_mlp_train(const float *__restrict__ P, 
         net_inputs(X, s, n, q, x);
         f32x4_t h1[4], h2[4], y;
         net_forward(L.w, c, q, x, h1, h2, y);
+        // the sums over the tile run over samples past the end too: theirs are zero
+        // (h1 is, by its inputs; h2 would hold b2, and a gradient of zero times an
+        // infinity is not zero)
+        if (s >= n) h2[0] = h2[1] = h2[2] = h2[3] = zero;
         // loss term and dL/dy through the trace projection: lane group 0 holds
         // components 0-3, group 1 components 4 and 5
         if (q == 0) {
