@@ -302,20 +302,27 @@ static void launch_gather(lesasm_mesh *m, int c0, int c1, double *rhs, hipStream
 // one gather): forking the type kernels onto streams and joining them costs
 // 20 us of events and gaps, more than it gains until the kernels are long.  In
 // one launch every type runs with the registers and LDS of the largest, which
-// costs the types that could hold more wavefronts (TET04, all types in FP32).
-// us in one launch against four, hybrid boxes: FP64 7 k elements 17/86, 0.26 M
-// 30/84, 1.0 M 78/95, 2.0 M 134/157, 4.0 M 251/270, 6.0 M 365/380, 9.9 M 591/598,
-// 20 M 1128/1130; FP32 1.0 M 67/84, 2.0 M 114/132, 3.0 M 166/169, 4.0 M 240/237,
-// 6.0 M 361/343; closure in FP32 2.0 M 275/313, 4.0 M 533/555, 6.0 M 808/822,
-// 9.9 M 1316/1318, in FP64 1.0 M 230/236, 2.0 M 401/422, 3.0 M 610/600, 6.0 M
-// 1228/1156.  Meshes of one type have nothing
-// to fork and keep that type's own kernel (2.0 M tetrahedra 65 against 74 us).
+// costs the types that could hold more wavefronts (TET04, all types in FP32; the
+// FP64 closure spills 104 registers, its PEN06 and HEX08 kernels alone 19 and 64).
+// us in one launch against four, hybrid boxes, a call repeated and one after
+// the caches were overwritten (both count: the lines lie where their sums meet):
+//   FP64          0.25 M 29/64, 46/75; 1.0 M 72/96, 94/106; 2.0 M 123/144, 157/169;
+//                 4.0 M 246/262, 284/292; 8.0 M 484/495, 513/514; 9.9 M 593/603, 615/617
+//                 (20 M, before the staging took its present form, 1128/1130)
+//   FP32          1.0 M 67/88, 92/105; 2.0 M 114/132, 159/163; 2.25 M 125/139, 176/172;
+//                 2.5 M 140/149, 194/183; 3.0 M 166/170, 222/208
+//   closure, FP32 2.0 M 266/304, 301/326; 4.0 M 518/539, 552/562; 8.0 M 1032/1046,
+//                 1067/1069; 9.9 M 1258/1263, 1293/1284
+//   closure, FP64 1.5 M 308/331, 353/362; 2.0 M 394/406, 445/438; 2.25 M 443/448,
+//                 497/484; 3.0 M 600/588, 649/617
+// Meshes of one type have nothing to fork and keep that type's own kernel (2.0 M
+// tetrahedra 65 against 74 us).
 static bool one_launch(const lesasm_mesh *m) {
     int types = 0;
     for (const Category &c : m->cat) types += c.n > 0;
     // (profiling, other workgroup sizes and the other options keep the kernels apart)
     if (types < 2 || !m->concurrent || m->profile || m->block != 256 || m->persist != 0) return false;
-    return m->n_elems <= ((m->precision == LESASM_PREC_FP64) != (m->mlp != nullptr) ? kOneLaunchLong : kOneLaunchShort);
+    return m->n_elems <= one_launch_limit(m->precision == LESASM_PREC_FP32, m->mlp != nullptr);
 }
 
 template <typename R, bool MLP>

@@ -521,7 +521,7 @@ bool batch_one_launch(const lesasm_batch *b, bool fp32) {
     int64_t elems = 0;
     for (int k = 0; k < kNumCat; ++k) types += b->type_off[k + 1] > b->type_off[k];
     for (const lesasm_mesh *m : b->meshes) elems += m->n_elems;
-    return types > 1 && elems <= (fp32 ? kOneLaunchShort : kOneLaunchLong);
+    return types > 1 && elems <= one_launch_limit(fp32, false);
 }
 
 void launch_items_all(lesasm_batch *b, const BatchCall &call, bool has_p, bool fp32, hipStream_t s) {

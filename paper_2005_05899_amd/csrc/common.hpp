@@ -133,9 +133,11 @@ int assemble_into(lesasm_mesh *m, const double *u, const double *p, double nu, d
 bool mesh_is_chunked(const lesasm_mesh *m);  // one of the chunked scatters
 ChunkViews chunk_views(const lesasm_mesh *m);
 // Elements up to which the chunks of several types run in one launch (the
-// measurements are at one_launch in assemble.hip): FP64 with Vreman's closure
-// and FP32 with the learned closure, and the other two.
-constexpr int64_t kOneLaunchLong = 10000000, kOneLaunchShort = 3000000;
+// measurements are at one_launch in assemble.hip).
+inline int64_t one_launch_limit(bool fp32, bool closure) {
+    if (fp32 == closure) return 10000000;  // FP64 with Vreman's closure, FP32 with the learned one
+    return fp32 ? 2500000 : 2100000;
+}
 bool mesh_is_periodic(const lesasm_mesh *m);  // field nodes apart from geometry nodes
 int launch_wall(lesasm_mesh *m, const double *u, double nu, double *rhs, hipStream_t s);
 
