@@ -59,3 +59,26 @@ def test_reported_iterations_are_those_run(cube, modes):
         st.pressure_solve(b)
         assert st.stats()[0] == modes - 1 and st.stats()[1] > 1e-2
         st.close()
+
+
+def test_many_tests_before_the_last(cube):
+    # six tests with iterations queued behind each: the oracle's residual is
+    # 3.3e-10 after 80 iterations and 3.0e-12 after 96.  One ulp in the matrix
+    # (its values are summed by atomics) moves these by up to 8.4e-14, hence the
+    # absolute 1e-12 on the residual
+    from oracle import cg, step
+    torch, lesasm = cube[:2]
+    c = mg.small_hybrid_case(nx=11, ny=9, layers=[(mg.HEX08, 2), (mg.PEN06, 2), (mg.TET04, 2), (mg.PYR05, 1)], seed=8)
+    m = lesasm.Mesh.from_arrays(c.mesh, c.vreman_c)
+    K = step.laplacian(c.mesh)
+    b = np.random.default_rng(5).standard_normal(m.n_field_nodes)
+    bd = m.to_internal(torch.from_numpy(b).cuda())
+    st = lesasm.Stepper(m, c.nu, 1e-3, rtol=1e-10, maxit=5000)
+    want, _, res_o = cg.jacobi_pcg(K, b, 96, rtol=0.0)
+    for _ in range(2):
+        x = m.to_user(st.pressure_solve(bd)).cpu().numpy()
+        it, res = st.stats()
+        assert it == 96 and res <= 1e-10 and abs(res - res_o) <= 1e-12
+        assert np.abs(x - want).max() <= 1e-9 * np.abs(want).max()
+    st.close()
+    m.close()
