@@ -307,6 +307,7 @@ __global__ __launch_bounds__(512) void k_scan_apply(unsigned long long *__restri
 // Running sums of the correction coefficients, Lambda_1 .. Lambda_(P-1), passed
 // by value up to kArgLambda parts.
 constexpr int kArgLambda = 256;
+constexpr int kLambdaPiece = 4096;  // sums of more parts are copied in pieces of this many
 struct LambdaArg {
     double v[kArgLambda];
 };
@@ -424,12 +425,14 @@ extern "C" int lesasm_sfc_partition(int64_t n, const double *d_cen, const int32_
     LambdaArg la{};
     const bool by_arg = h_lambda && P <= kArgLambda;
     if (h_lambda) {
-        std::vector<double> sums(by_arg ? 0 : P);
-        double *to = by_arg ? la.v : sums.data(), acc = 0.0;
-        for (int i = 0; i < P; ++i) to[i] = acc = acc + h_lambda[i];
-        if (!by_arg) {
-            LESASM_HIP_TRY(hipMemcpyAsync(w.lam, to, sizeof(double) * P, hipMemcpyHostToDevice, s));
+        double piece[kLambdaPiece], acc = 0.0;  // (no allocation that could throw)
+        double *to = by_arg ? la.v : piece;
+        for (int i = 0, k = 0; i < P; ++i) {
+            to[k++] = acc = acc + h_lambda[i];
+            if (by_arg || (k < kLambdaPiece && i + 1 < P)) continue;
+            LESASM_HIP_TRY(hipMemcpyAsync(w.lam + (i + 1 - k), piece, sizeof(double) * k, hipMemcpyHostToDevice, s));
             LESASM_HIP_TRY(hipStreamSynchronize(s));
+            k = 0;
         }
     }
     const int g = (int)((n - 1) / 256 + 1);
