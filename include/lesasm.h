@@ -155,20 +155,31 @@ int lesasm_mesh_filter_width(const lesasm_mesh *mesh, double *d_out, void *strea
 #define LESASM_OPT_CHECK_FINITE 3 /* 1: scan u and p for NaN/Inf first (synchronises) */
 #define LESASM_OPT_BLOCK 4        /* threads per block of the assembly kernels: 64, 128 or 256
                                      (default); with 256, FP32 contractions of chunks longer than
-                                     512 elements run in blocks of 512 */
-#define LESASM_OPT_PROFILE 5      /* 1: record HIP events around every kernel launch */
+                                     512 elements run in blocks of 512 (not in the one launch of
+                                     all types, see LESASM_OPT_CONCURRENT, which 64 and 128 switch
+                                     off) */
+#define LESASM_OPT_PROFILE 5      /* 1: record HIP events around every kernel launch; the element
+                                     types then have a kernel each also where a call without it
+                                     runs all of them in one launch, so the times are those of the
+                                     separate kernels */
 #define LESASM_OPT_CHUNK 6        /* elements per chunk of the chunked scatters, 32..4096, or 0
                                      (default) for 512 (64 below 16384 elements in the mesh, 128 below
                                      49152, 256 below 524288), 1024 for TET04 and PEN06 when that
                                      leaves at least 4096 chunks of the type;
                                      setting it rebuilds the chunks (synchronises) */
-#define LESASM_OPT_CONCURRENT 7   /* 1 (default): the element-type kernels of one chunked assembly run
-                                     concurrently on forked streams (joined before return); 0: one
-                                     after another on the caller's stream (isolated kernel timings) */
+#define LESASM_OPT_CONCURRENT 7   /* 1 (default): a staged mesh of several element types runs them in
+                                     one launch on the caller's stream up to 10 M elements (FP32
+                                     2.5 M; with a learned closure FP32 10 M, FP64 2.1 M), unless
+                                     LESASM_OPT_BLOCK, _PERSISTENT or _PROFILE differ from their
+                                     defaults; otherwise the element-type kernels of one chunked
+                                     assembly run concurrently on forked streams (joined before
+                                     return); 0: one after another on the caller's stream (isolated
+                                     kernel timings) */
 #define LESASM_OPT_PERSISTENT 8   /* 0 (default): one workgroup per chunk; 1: the chunk kernels launch
                                      as many workgroups as the GPU holds at once, each looping over
                                      chunks (measured slower: it blocks the concurrent type kernels);
-                                     N > 1: at most N workgroups (testing) */
+                                     N > 1: at most N workgroups (testing).  Not 0: the types are
+                                     not run in one launch */
 
 #define LESASM_PREC_FP64 0 /* whole element computation in FP64 */
 #define LESASM_PREC_FP32 1 /* element contractions in FP32 on coefficients formed in FP64
@@ -186,8 +197,9 @@ int lesasm_mesh_get_option(const lesasm_mesh *mesh, int option, int64_t *value);
  *   d_p    device [n_field_nodes] modified pressure, or NULL to drop grad p.
  *   nu     kinematic viscosity.
  *   dt     time step; used only in LESASM_RHS_INCREMENT mode.
- *   d_rhs  device [n_field_nodes][3], overwritten (zero-filled on the stream
- *          first, then scatter-added).  Must not alias d_u or d_p.
+ *   d_rhs  device [n_field_nodes][3], overwritten (every node stored once, or,
+ *          without staging rows, zero-filled on the stream first and then
+ *          added to).  Must not alias d_u or d_p.
  * Pointers must be 8-byte aligned.  Asynchronous on `stream`; a kernel fault
  * shows at the caller's next synchronisation.
  * Streams: calls on one mesh share its staging rows, events and counters.
@@ -214,7 +226,7 @@ int lesasm_assemble_momentum_rhs(lesasm_mesh *mesh, const double *d_u, const dou
 #define LESASM_NUM_KERNEL_SLOTS 7
 
 /* Per-slot sums of kernel durations (milliseconds, from HIP events recorded on
- * the caller's stream while LESASM_OPT_PROFILE is 1) and launch counts since
+ * the launch's stream while LESASM_OPT_PROFILE is 1) and launch counts since
  * the last reset.  In colour mode one launch per colour is counted.  Waits for
  * the recorded events (host synchronisation).  ms[] and launches[] are host
  * arrays of LESASM_NUM_KERNEL_SLOTS entries; reset != 0 clears the sums.     */
@@ -339,8 +351,9 @@ int lesasm_batch_get_config(const lesasm_batch *batch, int *chunk, int *order, i
  * ordered type by type (the chosen order kept inside each type) and four
  * persistent kernels, one per element type (each compiled, and resident, for
  * its own type), drain their parts concurrently on forked streams; 2 the same
- * type-ordered queue and four kernels, but one workgroup per item, scheduled
- * by the hardware (no queue counter; grid_per_cu does not apply).  Rebuilds
+ * type-ordered queue, but one workgroup per item, scheduled by the hardware
+ * (no queue counter; grid_per_cu does not apply), every type in one launch up
+ * to 10 M elements in the batch (FP32 2.5 M), else four kernels.  Rebuilds
  * the queue (synchronises).  Errors: LESASM_E_INVALID_ARG, LESASM_E_UNSUPPORTED
  * (a value other than 0, 1 or 2). */
 int lesasm_batch_set_per_type(lesasm_batch *batch, int per_type);
@@ -350,9 +363,10 @@ int lesasm_batch_get_per_type(const lesasm_batch *batch, int *per_type);
  * d_u[i] ([n_field_nodes_i][3]), d_p[i] (or d_p == NULL for none), nu[i],
  * d_rhs[i] (overwritten).  Same semantics as lesasm_assemble_momentum_rhs per
  * mesh (residual mode); all meshes use the first mesh's precision option.
- * Asynchronous: one small set-up kernel, the element kernel(s) and the
- * gathers of shared nodes (in the per-type layouts, the nodes of one type
- * only are gathered on that type's stream after its kernel).  A batch shares its members' staging rows: a call on
+ * Asynchronous: one small set-up kernel (layouts 0 and 1), the element
+ * kernel(s) and the gathers of shared nodes (where the types run on streams of
+ * their own, the nodes of one type only are gathered there after its kernel).
+ * A batch shares its members' staging rows: a call on
  * another stream than the previous call on the batch or on any member waits
  * for that call's end (as for lesasm_assemble_momentum_rhs). */
 int lesasm_batch_assemble(lesasm_batch *batch, const double *const *d_u, const double *const *d_p,

@@ -467,8 +467,8 @@ struct ClosureView {
 // and one or two others share its CU.  With ids, coordinates, velocities and
 // pressures of kStage nodes under way together, one index per node for the
 // write-back (d_fdst; before, the tag and then the staging slot) and that index
-// loaded before the last barrier, measured in us (one node and one list at a
-// time before): 20 M FP64 1240 -> 1155 (HEX08 352 -> 311, PEN06 534 -> 484,
+// loaded before the last barrier, measured in us (a call repeated on the same
+// fields; one node and one list at a time before): 20 M FP64 1240 -> 1155 (HEX08 352 -> 311, PEN06 534 -> 484,
 // TET04 165 -> 152, PYR05 84 -> 80), 20 M FP32 1037 -> 933, 2.0 M FP64
 // 138.7 -> 132, 2.0 M FP32 126.7 -> 113.8.  One node at a time with the lists
 // fused: 1189 / 949; three: 1153 / 941 (PYR05 FP32 66 instead of 61).

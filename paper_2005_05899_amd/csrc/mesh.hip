@@ -275,7 +275,14 @@ template <class T> static void dfree(lesasm_mesh *m, T *&p) {
 // hybrid boxes with chunks of 64, 128, 256, 512: 20.8 k elements 16.6, 17.1; 63 k
 // 21.1, 20.1, 18.2, 25.3; 0.26 M 49.7, 38.2, 29.3, 34.1; 0.49 M 87.0, 62.9, 47.0,
 // 44.6; 1.0 M 163, 112, 82.2, 77.9; 2.0 M -, 212, 147, 136 (768: 136).  (FP32, chosen
-// later than the chunks, has its best at 256 up to 4 M: 2.0 M 149, 105, 114.)
+// later than the chunks, has its best at 256 up to 4 M: 2.0 M 149, 105, 114 for a
+// call repeated on the same fields.)  Meshes of one type run that type's kernel
+// alone and take the same lengths; 256 against 512 there, FP64 and FP32: cube of
+// 0.26 M HEX08 46.2/45.2, 41.7/41.8, with the learned closure 125/175, 78/104; of
+// 0.51 M 76.9/74.0, 63.4/69.6; HEX08 box 0.26 M 45.5/56.0, 40.0/52.8; PEN06 0.30 M
+// 36.5/37.8, 31.1/33.3, 0.50 M 52.9/49.5, 40.8/43.2; PYR05 0.30 M 37.4/40.5,
+// 31.0/34.3; TET04 0.15 M 14.8/15.8, 0.41 M 22.1/22.2: 512 gains a few per cent in
+// FP64 towards the line and loses up to 40 elsewhere.
 static int chunk_length(const lesasm_mesh *m, int type, int64_t n) {
     if (m->chunk_elems) return m->chunk_elems;
     const int64_t all = m->n_elems;

@@ -110,8 +110,10 @@ __device__ __forceinline__ void net_forward(const NetLds &w, int c, int q, const
 // samples), which stay in accumulators over the workgroup's tiles.  The sums of
 // one workgroup go to partial[b] (the parameters' order, then the loss), and
 // k_mlp_grad_reduce adds the workgroups in a fixed order.
-// Bound by the chain of about 260 dependent-by-layer FP32 matrix instructions
-// a tile (32 cycles each: 3.5 us), not by bytes (64 B a sample).  The kernels
+// Bound by latency, not by bytes (64 B a sample): of 17 us with one tile a
+// workgroup the 268 FP32 matrix instructions of a wavefront take 3.6 (32 cycles
+// each), the rest is the parameters' and samples' way into LDS and the layers'
+// dependences (waiting 0.60 of the wave time).  The kernels
 // it replaces kept H1, H2 and their gradients in memory (1052 B a sample) and
 // summed each weight's gradient over all samples in one thread: loss and
 // gradients of 8192 samples 17 against 2064 us (call to call, host included),

@@ -10,8 +10,9 @@
 //   K dp   = -(1/dt) D u*   (right-hand side projected to zero mean; dp zero mean)
 //   u^n+1  = u* - dt M_L^-1 G dp,   p^n+1 = p^n + dp
 // with K = int grad N_a . grad N_b, (D u)_a = int N_a div u, (G p)_a = int N_a grad p.
-// Everything is FP64.  These are support operations for the assembly; their
-// element loops use direct FP64 atomics.
+// Everything is FP64.  The Laplacian's values, and divergence and gradient on
+// meshes without chunks, are added with device atomics; on chunked meshes these
+// two sum a chunk's nodes in LDS first.
 #include <algorithm>
 #include <cmath>
 
